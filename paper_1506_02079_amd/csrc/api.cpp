@@ -1758,7 +1758,13 @@ static SmoothArgs smooth_args(const uint8_t *stack, int S, int H, int W, long lo
     a.H = H;
     a.W = W;
     a.rxy = sigma_xy > 0 ? (int)std::floor(3.0 * sigma_xy) : 0;
-    a.rz = sigma_z > 0 ? (int)std::floor(3.0 * sigma_z) : 0;
+    // The taps that can fall inside the stack: no slice is more than S - 1 away
+    // from another, so a thin stack takes the kernel of that radius.  Its march
+    // is S + radius + 1 steps long and its ring 2 radius + 1 planes; the taps
+    // left out only ever met slices outside the stack, so every sum is the same.
+    // (2 x 21504 x 26624 at radius 9: 12 steps, 8.5 ms; at radius 1: 4 steps,
+    // 5.7 ms.)
+    a.rz = sigma_z > 0 ? std::min((int)std::floor(3.0 * sigma_z), S - 1) : 0;
     for (int d = 0; d <= a.rxy; ++d)
         a.wxy[d] = sigma_xy > 0 ? std::exp(-(double)d * d / (2 * sigma_xy * sigma_xy)) : 1.0;
     for (int d = 0; d <= a.rz; ++d)
