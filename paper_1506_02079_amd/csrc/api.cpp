@@ -230,6 +230,8 @@ struct Plan {
     int list_down[kMaxLevels], list_up[kMaxLevels], list_coarse[kMaxLevels];
     int max_level = 0;
     std::vector<int> ranges_cycle, ranges_tiles, ranges_ftiles, ranges_smooth;
+    // longest per-slice range of each (sizes the reduction blocks)
+    int max_cycle = 0, max_tiles = 0, max_ftiles = 0, max_smooth = 0, max_p0 = 0;
     int n_norm;
     std::vector<SliceIO> io;
     long long n_tiles = 0;
@@ -528,6 +530,16 @@ gdf_status make_plan(Plan &P, int n, const std::vector<int> &H, const std::vecto
         }
         P.n_partd = std::max<long long>(P.n_partd, nparts * n);
     }
+    auto longest = [](const std::vector<int> &r) {
+        int m = 0;
+        for (size_t i = 0; i + 1 < r.size(); i += 2) m = std::max(m, r[i + 1] - r[i]);
+        return m;
+    };
+    P.max_cycle = longest(P.ranges_cycle);
+    P.max_tiles = longest(P.ranges_tiles);
+    P.max_ftiles = longest(P.ranges_ftiles);
+    P.max_smooth = longest(P.ranges_smooth);
+    P.max_p0 = longest(P.ranges_p0);
     if (P.n_partd > 0x7fffffffLL || P.items.size() > 0x7fffffffULL || P.n_pitems > 0x7fffffffLL)
         return set_err(GDF_EUNSUPPORTED, "problem too large for 32-bit work indices");
     // layout: [tables][partials][gs copy][arena]
@@ -914,12 +926,17 @@ struct Run {
     // hair below the exact FP64 residual of the output, which is checked after.
     // (in-loop checks -- strip partials, or FP64 partials with the sums of r --
     // use the working-precision residual)
+    int max_slots(const int *range) const
+    {
+        return range == r_cycle ? P.max_cycle : range == r_tiles ? P.max_tiles : range == r_ftiles ? P.max_ftiles
+             : range == r_smooth ? P.max_smooth : P.max_p0;
+    }
     gdf_status finish(const int *range, const float2 *pf, const double *pd, int mode, int count,
                       const double *pd2 = nullptr)
     {
         const bool in_loop = mode == FIN_CHECK && (pf || pd2);
         const double t = in_loop ? 0.99 * tol : tol;
-        HIP_TRY(launch_finish(P.n, range, pf, pd, pd2, mode, t, max_cycles, count, in_loop ? stall_ratio : 0.0, st,
+        HIP_TRY(launch_finish(P.n, max_slots(range), range, pf, pd, pd2, mode, t, max_cycles, count, in_loop ? stall_ratio : 0.0, st,
                               active, s));
         return GDF_OK;
     }
@@ -1883,9 +1900,9 @@ static gdf_status fuse_stack_plain(const uint8_t *stack_all, int S_all, int H, i
             // from the b_u the smoothing wrote and the stack
             HIP_TRY(launch_pprep(P.fp64, P.fp64 ? GDF_F64 : GDF_F32, nullptr, GDF_U8, stack, R.io, R.plaunch(0),
                                  R.partd, R.partd2, R.partd3, s));
-            HIP_TRY(launch_finish_rhs(P.n, R.r_p0, R.partd, R.partd2, R.partd3, R.st, s));
+            HIP_TRY(launch_finish_rhs(P.n, P.max_p0, R.r_p0, R.partd, R.partd2, R.partd3, R.st, s));
         } else {
-            HIP_TRY(launch_finish_rhs(P.n, R.r_smooth, R.partd, R.partd2, R.partd3, R.st, s));
+            HIP_TRY(launch_finish_rhs(P.n, P.max_smooth, R.r_smooth, R.partd, R.partd2, R.partd3, R.st, s));
         }
         return solve_body(R, x);
     };
@@ -2219,7 +2236,7 @@ static gdf_status solve_slices_plain(int n, const gdf_slice_desc *d, int gs_dtyp
                 HIP_TRY(launch_prep(P.fp64, gs_dtype, gs, go_dtype, go, R.io, n, P.n_tiles, R.desc, R.partd,
                                     R.partd2, R.partd3, s));
         }
-        HIP_TRY(launch_finish_rhs(n, P.periodic ? R.r_p0 : R.r_tiles, R.partd, R.partd2, R.partd3, R.st, s));
+        HIP_TRY(launch_finish_rhs(n, P.periodic ? P.max_p0 : P.max_tiles, P.periodic ? R.r_p0 : R.r_tiles, R.partd, R.partd2, R.partd3, R.st, s));
         return solve_body(R, x);
     };
 
@@ -2342,7 +2359,7 @@ static gdf_status backward_plain(int n, const gdf_slice_desc *d, int dtype, cons
         ProfScope ps(PC_PREP, 0.0, s, false);
         HIP_TRY(launch_prep_adjoint(P.fp64, grad_f, R.io, n, P.n_tiles, R.desc, R.partd, R.partd3, s));
     }
-    HIP_TRY(launch_finish_rhs(n, R.r_tiles, R.partd, R.partd, R.partd3, R.st, s));
+    HIP_TRY(launch_finish_rhs(n, P.max_tiles, R.r_tiles, R.partd, R.partd, R.partd3, R.st, s));
     if (P.mixed) {
         if ((r = mixed_iterate(R, dtype, nullptr, GDF_F32, nullptr, grad_f))) return r;
     } else {

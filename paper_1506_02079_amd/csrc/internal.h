@@ -208,7 +208,8 @@ enum FinishMode {
 };
 
 // Sum the partials of each slice over [range[2s], range[2s+1]) in a fixed
-// order (deterministic) and update the slice state and flags.
+// order (deterministic) and update the slice state and flags.  max_slots: the
+// longest of these ranges (sizes the blocks; any value is correct).
 // partials_f: strip partials (r^2, r); partials_d: FP64 tile partials.
 // FIN_CHECK with strip partials also records the constant-mode correction.
 // FIN_CHECK with stall_ratio > 0: from the second counted cycle on, a slice
@@ -216,13 +217,13 @@ enum FinishMode {
 // above tol) stops with state.stalled = 1 (the working precision's floor).
 // partials_d2 (with partials_d, FIN_CHECK): FP64 partial sums of r, giving
 // the constant-mode correction as the strip partials do.
-hipError_t launch_finish(int n_slices, const int *range, const float2 *partials_f,
+hipError_t launch_finish(int n_slices, int max_slots, const int *range, const float2 *partials_f,
                          const double *partials_d, const double *partials_d2, int mode, double tol,
                          int max_cycles, int count_cycle, double stall_ratio, SliceState *state, int *active,
                          hipStream_t s);
 
 // FIN_BB, FIN_INIT and FIN_MEAN of one right-hand side in one launch.
-hipError_t launch_finish_rhs(int n_slices, const int *range, const double *pbb, const double *pb0,
+hipError_t launch_finish_rhs(int n_slices, int max_slots, const int *range, const double *pbb, const double *pb0,
                              const double *pbs, SliceState *state, hipStream_t s);
 
 // After the exact residual of the output (FIN_FINAL): slices whose FP64

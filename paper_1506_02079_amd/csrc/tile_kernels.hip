@@ -166,29 +166,70 @@ __device__ __forceinline__ bool quad_ctx(const SliceIO *io, int n, long long n_t
 // ------------------------------------------------------------- finish ---
 
 // One block per slice; fixed-order strided sum then a fixed tree, so the
-// result does not depend on scheduling.
-__global__ __launch_bounds__(256) void finish_kernel(int n_slices, const int *range,
-                                                     const float2 *pf, const double *pd, const double *pd2,
-                                                     int mode, double tol, int max_cycles, int count_cycle,
-                                                     double stall_ratio, SliceState *st, int *active)
+// result does not depend on scheduling.  The kernels are a chain of dependent
+// loads on as many CUs as there are slices: each thread keeps kFinLoads
+// independent loads in flight, and slices with many partial sums take NT =
+// 1024 threads (launch_finish*).  2 slices of 559104 partials: 0.93 ms
+// with 256 threads and one load in flight each, 0.10 ms now.
+constexpr int kFinLoads = 8;
+
+// Sum over an NT-thread block in a fixed order (butterfly within each wave,
+// then the wave sums in order).
+template <int NT> __device__ double block_sum_n(double v, double *red)
 {
-    __shared__ double red[4];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    double r = 0.0;
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) r += red[w];
+    __syncthreads();
+    return r;
+}
+
+// sum over i in [b0, b1) of get(i) by the block's threads: thread-strided
+// elements, kFinLoads accumulators per thread added in order
+template <int NT, class Get> __device__ __forceinline__ double strided_sum(int b0, int b1, Get get)
+{
+    double acc[kFinLoads];
+#pragma unroll
+    for (int k = 0; k < kFinLoads; ++k) acc[k] = 0.0;
+    for (long long i = (long long)b0 + threadIdx.x; i < b1; i += kFinLoads * NT)
+#pragma unroll
+        for (int k = 0; k < kFinLoads; ++k) {
+            // (clamped, unconditional loads: they all start before the first is waited for)
+            const long long j = i + (long long)k * NT;
+            const double x = get((int)(j < b1 ? j : i));
+            acc[k] += j < b1 ? x : 0.0;
+        }
+    double v = acc[0];
+#pragma unroll
+    for (int k = 1; k < kFinLoads; ++k) v += acc[k];
+    return v;
+}
+
+template <int NT>
+__global__ __launch_bounds__(NT) void finish_kernel(int n_slices, const int *range,
+                                                    const float2 *pf, const double *pd, const double *pd2,
+                                                    int mode, double tol, int max_cycles, int count_cycle,
+                                                    double stall_ratio, SliceState *st, int *active)
+{
+    __shared__ double red[NT / 64];
     const int sidx = blockIdx.x;
     if (sidx >= n_slices) return;
     const int b0 = range[2 * sidx], b1 = range[2 * sidx + 1];
     double v = 0.0, w = 0.0;
-    for (int i = b0 + threadIdx.x; i < b1; i += blockDim.x) {
-        if (pf) {
-            v += (double)pf[i].x;
-            w += (double)pf[i].y;
-        } else {
-            v += pd[i];
-            if (pd2) w += pd2[i];
-        }
+    if (pf) {
+        v = strided_sum<NT>(b0, b1, [=](int i) { return (double)pf[i].x; });
+        w = strided_sum<NT>(b0, b1, [=](int i) { return (double)pf[i].y; });
+    } else {
+        v = strided_sum<NT>(b0, b1, [=](int i) { return pd[i]; });
+        if (pd2) w = strided_sum<NT>(b0, b1, [=](int i) { return pd2[i]; });
     }
     const bool has_r = pf || pd2;   // (uniform)
-    const double sum = block_sum(v, red);
-    const double rsum = has_r ? block_sum(w, red) : 0.0;
+    const double sum = block_sum_n<NT>(v, red);
+    const double rsum = has_r ? block_sum_n<NT>(w, red) : 0.0;
     if (threadIdx.x != 0) return;
     SliceState &S = st[sidx];
     switch (mode) {
@@ -227,20 +268,18 @@ __global__ __launch_bounds__(256) void finish_kernel(int n_slices, const int *ra
 
 // The three sums after right-hand-side formation in one launch: ||b||^2,
 // rel_init = sqrt(||b_u||^2 / ||b||^2), and the mean of b_u (bmean, uoff).
-__global__ __launch_bounds__(256) void finish_rhs_kernel(int n_slices, const int *range, const double *pbb,
-                                                         const double *pb0, const double *pbs, SliceState *st)
+template <int NT>
+__global__ __launch_bounds__(NT) void finish_rhs_kernel(int n_slices, const int *range, const double *pbb,
+                                                        const double *pb0, const double *pbs, SliceState *st)
 {
-    __shared__ double red[4];
+    __shared__ double red[NT / 64];
     const int sidx = blockIdx.x;
     if (sidx >= n_slices) return;
     const int b0 = range[2 * sidx], b1 = range[2 * sidx + 1];
-    double v = 0.0, w = 0.0, x = 0.0;
-    for (int i = b0 + threadIdx.x; i < b1; i += blockDim.x) {
-        v += pbb[i];
-        w += pb0[i];
-        x += pbs[i];
-    }
-    const double sbb = block_sum(v, red), sb0 = block_sum(w, red), sbs = block_sum(x, red);
+    const double v = strided_sum<NT>(b0, b1, [=](int i) { return pbb[i]; });
+    const double w = strided_sum<NT>(b0, b1, [=](int i) { return pb0[i]; });
+    const double x = strided_sum<NT>(b0, b1, [=](int i) { return pbs[i]; });
+    const double sbb = block_sum_n<NT>(v, red), sb0 = block_sum_n<NT>(w, red), sbs = block_sum_n<NT>(x, red);
     if (threadIdx.x != 0) return;
     SliceState &S = st[sidx];
     S.bb = sbb;
@@ -249,22 +288,33 @@ __global__ __launch_bounds__(256) void finish_rhs_kernel(int n_slices, const int
     S.uoff = S.bmean / S.alpha;
 }
 
-hipError_t launch_finish_rhs(int n_slices, const int *range, const double *pbb, const double *pb0,
+// A slice with more partial sums than this takes a 1024-thread block: 256
+// threads then need more than one trip of kFinLoads loads.
+constexpr int kFinWide = 256 * kFinLoads;
+
+hipError_t launch_finish_rhs(int n_slices, int max_slots, const int *range, const double *pbb, const double *pb0,
                              const double *pbs, SliceState *state, hipStream_t s)
 {
     if (n_slices <= 0) return hipSuccess;
-    hipLaunchKernelGGL(finish_rhs_kernel, dim3(n_slices), dim3(256), 0, s, n_slices, range, pbb, pb0, pbs, state);
+    if (max_slots > kFinWide)
+        hipLaunchKernelGGL(finish_rhs_kernel<1024>, dim3(n_slices), dim3(1024), 0, s, n_slices, range, pbb, pb0, pbs, state);
+    else
+        hipLaunchKernelGGL(finish_rhs_kernel<256>, dim3(n_slices), dim3(256), 0, s, n_slices, range, pbb, pb0, pbs, state);
     return hipGetLastError();
 }
 
-hipError_t launch_finish(int n_slices, const int *range, const float2 *partials_f,
+hipError_t launch_finish(int n_slices, int max_slots, const int *range, const float2 *partials_f,
                          const double *partials_d, const double *partials_d2, int mode, double tol,
                          int max_cycles, int count_cycle, double stall_ratio, SliceState *state, int *active,
                          hipStream_t s)
 {
     if (n_slices <= 0) return hipSuccess;
-    hipLaunchKernelGGL(finish_kernel, dim3(n_slices), dim3(256), 0, s, n_slices, range, partials_f,
-                       partials_d, partials_d2, mode, tol, max_cycles, count_cycle, stall_ratio, state, active);
+    if (max_slots > kFinWide)
+        hipLaunchKernelGGL(finish_kernel<1024>, dim3(n_slices), dim3(1024), 0, s, n_slices, range, partials_f,
+                           partials_d, partials_d2, mode, tol, max_cycles, count_cycle, stall_ratio, state, active);
+    else
+        hipLaunchKernelGGL(finish_kernel<256>, dim3(n_slices), dim3(256), 0, s, n_slices, range, partials_f,
+                           partials_d, partials_d2, mode, tol, max_cycles, count_cycle, stall_ratio, state, active);
     return hipGetLastError();
 }
 
