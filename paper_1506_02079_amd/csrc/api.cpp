@@ -66,7 +66,6 @@ constexpr double kSigmaLight = 0.05;
 // An FP32 V-cycle that shrinks the residual by less than this factor (the
 // usual factor is 0.05 - 0.3) means the iterate has reached FP32's floor.
 constexpr double kStallRatio = 0.6;
-constexpr int kCoarsePasses = 1;   // x 2 sweeps on the coarsest level (sigma >= 2: enough)
 constexpr int kTileW = 64, kTileH = 16;
 constexpr size_t kAlign = 256;
 
@@ -206,7 +205,15 @@ struct List {
     int off, count;            // all items: [off, off + count) = interior, column-edge, guarded
     int n_fast, n_rows_in;
     int G, VW, TH;
-    int csw;                   // sweeps per smoothing step of this list's passes (coarse levels)
+    std::vector<std::pair<int, double>> slice_px;   // (slice, pixels at this level)
+};
+
+// A work list of register-block passes over one level: the slices that have a
+// coarser level, or those for which it is the coarsest.
+struct BList {
+    int off = 0, count = 0;
+    int sweeps = 0;            // sweeps per smoothing step
+    int G = 0;                 // halo of the regions
     std::vector<std::pair<int, double>> slice_px;   // (slice, pixels at this level)
 };
 
@@ -227,11 +234,15 @@ struct Plan {
     std::vector<Item> items;
     std::vector<List> lists;
     int list_first = -1, list_fine = -1, list_single = -1;
-    int list_down[kMaxLevels], list_up[kMaxLevels], list_coarse[kMaxLevels];
+    // register-block passes: [level], slices with a coarser level (mid) and slices
+    // whose coarsest level it is (last); level 0 only when periodic
+    std::vector<BItem> bitems;
+    BList bmid[kMaxLevels], blast[kMaxLevels];
+    long long n_bres = 0;      // items reserved in the workspace (either boundary)
     int max_level = 0;
     std::vector<int> ranges_cycle, ranges_tiles, ranges_ftiles, ranges_smooth;
     // longest per-slice range of each (sizes the reduction blocks)
-    int max_cycle = 0, max_tiles = 0, max_ftiles = 0, max_smooth = 0, max_p0 = 0;
+    int max_cycle = 0, max_tiles = 0, max_ftiles = 0, max_smooth = 0;
     int n_norm;
     std::vector<SliceIO> io;
     long long n_tiles = 0;
@@ -239,19 +250,14 @@ struct Plan {
     long long n_partd = 0;
     bool mixed = false;
     bool need_gs_copy = false;   // fuse_stack MIXED without g_smooth output
-    // periodic boundaries: tiles of every level (list l = all slices having
-    // level l, the slices with a level below l first: pmid[l] items); level
-    // 0's per-slice slot ranges.  Every plan reserves the tables and partial
-    // sums they need, so workspace sizes do not depend on the boundary.
+    // periodic boundaries: the per-pixel kernels' table.  Every plan reserves the tables and partial sums of either
+    // boundary, so workspace sizes do not depend on it.
     bool periodic = false;
-    std::vector<PItem> pitems;
-    int poff[kMaxLevels], pcnt[kMaxLevels], pmid[kMaxLevels];
-    std::vector<int> ranges_p0;
-    long long n_pitems = 0, n_p0 = 0;
+    std::vector<int> ptiles;   // the slice of each tile
     // layout (bytes from the workspace base)
     size_t off_tables, tables_bytes;
     size_t off_state, off_active, off_only, off_done, off_desc, off_items, off_r_cycle, off_r_tiles, off_r_ftiles,
-        off_r_smooth, off_io, off_u64tab, off_pitems, off_r_p0;
+        off_r_smooth, off_io, off_u64tab, off_bitems, off_ptiles;
     size_t off_partf, off_partd, off_partd2, off_partd3, off_gscopy, off_arena, arena_bytes, total;
 };
 
@@ -261,63 +267,42 @@ struct Plan {
 // end of the pass.  (Measured on 64 x 2048^2 stacks at alpha 0.001, 0.01 and
 // 0.1: 80 rows beat 64, 72, 88, 96, 112, 128 and taller on level 0, by 1-4% of
 // the whole step against 128.)
-int choose_rows(const Plan &P, const std::vector<int> &slices, int level, StripKind kind, int G, int VW, int csw)
+int choose_rows(const Plan &P, const std::vector<int> &slices, StripKind kind, int G, int VW)
 {
-    if (level == 0 && P.o.tile_rows) return P.o.tile_rows;
-    int slots = strip_resident_waves(kind, csw, P.o.fsw, P.fp64);
+    if (P.o.tile_rows) return P.o.tile_rows;
+    int slots = strip_resident_waves(kind, P.o.fsw, P.fp64);
     if (slots <= 0) slots = 4096;
     const int E = (G + 2) & ~1;
-    // Coarse levels start from 64-row items, 32 on levels of at most 256 rows,
-    // and are halved only for batches far too small to fill the GPU: their
-    // passes are bound by the serial row march of each item, so many short
-    // items (each re-walking its halo rows) lose to fewer taller ones (on the
-    // 64 x 2048^2 stack 16-row items on levels 2 and 3 make the coarse levels
-    // 18% slower, and so do 128-row items everywhere)
     int th = 80;
-    double want = 2.0 * slots;   // level 0: items that fill the GPU twice over
-    if (level > 0) {
-        int hmax = 0;
-        for (int s : slices) hmax = std::max(hmax, P.g[s].h[level]);
-        th = hmax <= 256 ? 32 : 64;
-        want = slots / 16.0;
-    }
     for (; th / 2 >= 16; th /= 2) {
         double items = 0.0;
         for (int s : slices) {
-            const int H = P.g[s].h[level], W = P.g[s].w[level];
+            const int H = P.g[s].H, W = P.g[s].W;
             const int lo = E, hi = (H - E) & ~1;
             const int nb = hi - lo >= th ? 2 + (hi - lo + th - 1) / th : (H + th - 1) / th;
             items += (double)((W + VW - 1) / VW) * nb;
         }
-        if (items >= want) break;
+        if (items >= 2.0 * slots) break;
     }
     return th;
 }
 
-int add_list(Plan &P, StripKind kind, int level, const std::vector<int> &slices)
+int add_list(Plan &P, StripKind kind, const std::vector<int> &slices)
 {
     if (slices.empty()) return -1;
     List L;
     L.kind = kind;
+    const int level = 0;
     L.level = level;
-    // coarse sweeps by default: nu + 1, and nu on levels where every slice's
-    // screening coefficient is at least kSigmaLight (there the extra sweep
-    // buys no cycles)
-    L.csw = P.o.csw;
-    if (P.o.csw_auto && (kind == SK_DOWN || kind == SK_UP)) {
-        double smin = 1e300;
-        for (int sl : slices) smin = std::min(smin, P.g[sl].sigma[level]);
-        if (smin >= kSigmaLight) L.csw = P.o.nu;
-    }
-    L.G = strip_halo(kind, L.csw, P.o.fsw);
+    L.G = strip_halo(kind, P.o.fsw);
     L.VW = kStripCols - 2 * L.G;
-    L.TH = choose_rows(P, slices, level, kind, L.G, L.VW, L.csw);
+    L.TH = choose_rows(P, slices, kind, L.G, L.VW);
     // the rows an item touches must span less than 2^31 bytes (the kernel
     // addresses them with 32-bit offsets); with W <= kMaxWidth this leaves at
     // least 16 rows per item
     int maxp = 0;
     for (int s : slices) maxp = std::max(maxp, P.g[s].pitch[level]);
-    const long long row_bytes = (long long)maxp * (level == 0 ? P.esz : P.csz);
+    const long long row_bytes = (long long)maxp * P.esz;
     const long long rmax = (0x7FFFFFFFLL / row_bytes - 2 * L.G - 4) & ~1LL;
     if (L.TH > rmax) L.TH = (int)std::max<long long>(16, rmax);
     L.off = (int)P.items.size();
@@ -359,6 +344,24 @@ int add_list(Plan &P, StripKind kind, int level, const std::vector<int> &slices)
     L.count = (int)P.items.size() - L.off;
     P.lists.push_back(L);
     return (int)P.lists.size() - 1;
+}
+
+// Work list of the register-block passes of one level over `slices`.
+BList add_blocks(Plan &P, int level, const std::vector<int> &slices, int sweeps, int G)
+{
+    BList B;
+    B.off = (int)P.bitems.size();
+    B.sweeps = sweeps;
+    B.G = G;
+    for (int s : slices) {
+        const int H = P.g[s].h[level], W = P.g[s].w[level];
+        B.slice_px.emplace_back(s, (double)H * W);
+        const int nx = block_tiles(W, kBlockCols, G, P.periodic), ny = block_tiles(H, kBlockRows, G, P.periodic);
+        for (int ty = 0; ty < ny; ++ty)
+            for (int tx = 0; tx < nx; ++tx) P.bitems.push_back(BItem{P.desc_base[s] + level, tx, ty});
+    }
+    B.count = (int)P.bitems.size() - B.off;
+    return B;
 }
 
 // per-slice [begin, end) of a list's partial-sum slots
@@ -439,21 +442,44 @@ gdf_status make_plan(Plan &P, int n, const std::vector<int> &H, const std::vecto
         }
     }
     // work lists
-    for (int l = 0; l < kMaxLevels; ++l) P.list_down[l] = P.list_up[l] = P.list_coarse[l] = -1;
     std::vector<int> mid0, single0;
     for (int s = 0; s < n; ++s) (P.g[s].nlev > 1 ? mid0 : single0).push_back(s);
-    P.list_first = add_list(P, SK_FIRST_RESTRICT, 0, mid0);
-    P.list_fine = add_list(P, SK_FINE, 0, mid0);
-    P.list_single = add_list(P, SK_SINGLE, 0, single0);
-    for (int l = 1; l <= P.max_level; ++l) {
-        std::vector<int> mid, coarsest;
+    P.list_first = add_list(P, SK_FIRST_RESTRICT, mid0);
+    P.list_fine = add_list(P, SK_FINE, mid0);
+    P.list_single = add_list(P, SK_SINGLE, single0);
+    for (int l = 0; l <= P.max_level; ++l) {
+        std::vector<int> mid, last;
         for (int s = 0; s < n; ++s) {
             if (P.g[s].nlev - 1 > l) mid.push_back(s);
-            else if (P.g[s].nlev - 1 == l) coarsest.push_back(s);
+            else if (P.g[s].nlev - 1 == l) last.push_back(s);
         }
-        P.list_down[l] = add_list(P, SK_DOWN, l, mid);
-        P.list_up[l] = add_list(P, SK_UP, l, mid);
-        P.list_coarse[l] = add_list(P, SK_COARSE, l, coarsest);
+        // coarse sweeps by default: nu + 1, and (Neumann) nu on levels where every
+        // slice's screening coefficient is at least kSigmaLight (there the extra
+        // sweep buys no cycles)
+        const int psw = l == 0 ? o.nu : o.csw;
+        int nsw = o.csw;
+        if (o.csw_auto) {
+            double smin = 1e300;
+            for (int sl : mid) smin = std::min(smin, P.g[sl].sigma[l]);
+            if (smin >= kSigmaLight) nsw = o.nu;
+        }
+        const int gp = block_halo(psw), gn = block_halo(nsw);
+        constexpr int gl = 4;   // the Neumann coarsest level's pass: 2 sweeps, no residual
+        // (reserved for either boundary and any sweep count: the widest halo, the
+        // untrimmed periodic tiling)
+        constexpr int gmax = block_halo(3);
+        for (const auto *v : {&mid, &last})
+            for (int s : *v)
+                P.n_bres += (long long)block_tiles(P.g[s].w[l], kBlockCols, gmax, true) *
+                            block_tiles(P.g[s].h[l], kBlockRows, gmax, true);
+        if (P.n_bres > 0x7fffffffLL) return set_err(GDF_EUNSUPPORTED, "problem too large for 32-bit work indices");
+        if (P.periodic) {
+            P.bmid[l] = add_blocks(P, l, mid, psw, gp);
+            P.blast[l] = add_blocks(P, l, last, psw, gp);
+        } else if (l > 0) {
+            P.bmid[l] = add_blocks(P, l, mid, nsw, gn);
+            P.blast[l] = add_blocks(P, l, last, 2, gl);
+        }
     }
     const int nC = P.list_fine >= 0 ? P.lists[P.list_fine].count : 0;
     const int nS = P.list_single >= 0 ? P.lists[P.list_single].count : 0;
@@ -461,6 +487,15 @@ gdf_status make_plan(Plan &P, int n, const std::vector<int> &H, const std::vecto
     P.ranges_cycle.assign(2 * n, -1);
     list_ranges(P, P.list_fine, 0, P.ranges_cycle);
     list_ranges(P, P.list_single, nC, P.ranges_cycle);
+    if (P.periodic) {   // norm partials: the block items of level 0 (one level-0 list after the other)
+        P.ranges_cycle.assign(2 * n, 0);
+        const int n0 = P.bmid[0].count + P.blast[0].count;
+        for (int i = 0; i < n0; ++i) {
+            const int s = P.descs[P.bitems[P.bmid[0].off + i].lev].slice;
+            if (i == 0 || P.bitems[P.bmid[0].off + i - 1].lev != P.bitems[P.bmid[0].off + i].lev) P.ranges_cycle[2 * s] = i;
+            P.ranges_cycle[2 * s + 1] = i + 1;
+        }
+    }
     // tiles for the per-pixel kernels
     P.io.resize(n);
     P.ranges_tiles.resize(2 * n);
@@ -488,37 +523,8 @@ gdf_status make_plan(Plan &P, int n, const std::vector<int> &H, const std::vecto
     P.n_tiles = tb;
     P.n_ftiles = fb;
     P.n_partd = tb;
-    // periodic tiles (counted for every plan, built for periodic ones)
-    auto ptiles = [&](int s, int l) {
-        return (long long)((P.g[s].h[l] + kPTileH - 1) / kPTileH) * ((P.g[s].w[l] + kPTileW - 1) / kPTileW);
-    };
-    for (int s = 0; s < n; ++s)
-        for (int l = 0; l < P.g[s].nlev; ++l) {
-            P.n_pitems += ptiles(s, l);
-            if (l == 0) P.n_p0 += ptiles(s, l);
-        }
-    P.n_partd = std::max(P.n_partd, P.n_p0);
-    P.ranges_p0.assign(2 * n, 0);
-    for (int l = 0; l < kMaxLevels; ++l) P.poff[l] = P.pcnt[l] = P.pmid[l] = 0;
-    if (P.periodic) {
-        std::vector<int> order(n);
-        for (int s = 0; s < n; ++s) order[s] = s;
-        std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return P.g[a].nlev > P.g[b].nlev; });
-        for (int l = 0; l <= P.max_level; ++l) {
-            P.poff[l] = (int)P.pitems.size();
-            for (int s : order) {
-                const SliceGeom &g = P.g[s];
-                if (g.nlev <= l) continue;
-                if (l == 0) P.ranges_p0[2 * s] = (int)P.pitems.size() - P.poff[0];
-                for (int y0 = 0; y0 < g.h[l]; y0 += kPTileH)
-                    for (int x0 = 0; x0 < g.w[l]; x0 += kPTileW)
-                        P.pitems.push_back(PItem{P.desc_base[s] + l, s, x0, y0});
-                if (l == 0) P.ranges_p0[2 * s + 1] = (int)P.pitems.size() - P.poff[0];
-                if (g.nlev > l + 1) P.pmid[l] = (int)P.pitems.size() - P.poff[l];
-            }
-            P.pcnt[l] = (int)P.pitems.size() - P.poff[l];
-        }
-    }
+    if (P.periodic)
+        for (int s = 0; s < n; ++s) P.ptiles.insert(P.ptiles.end(), P.ranges_tiles[2 * s + 1] - P.ranges_tiles[2 * s], s);
     if (smooth_S > 0) {
         // smoothing partials: [S][tiles]
         const long long nparts = (long long)((W[0] + kSmoothTileW - 1) / kSmoothTileW) *
@@ -539,8 +545,7 @@ gdf_status make_plan(Plan &P, int n, const std::vector<int> &H, const std::vecto
     P.max_tiles = longest(P.ranges_tiles);
     P.max_ftiles = longest(P.ranges_ftiles);
     P.max_smooth = longest(P.ranges_smooth);
-    P.max_p0 = longest(P.ranges_p0);
-    if (P.n_partd > 0x7fffffffLL || P.items.size() > 0x7fffffffULL || P.n_pitems > 0x7fffffffLL)
+    if (P.n_partd > 0x7fffffffLL || P.items.size() > 0x7fffffffULL)
         return set_err(GDF_EUNSUPPORTED, "problem too large for 32-bit work indices");
     // layout: [tables][partials][gs copy][arena]
     size_t o2 = 0;
@@ -554,12 +559,13 @@ gdf_status make_plan(Plan &P, int n, const std::vector<int> &H, const std::vecto
     P.off_items = take(sizeof(Item) * std::max<size_t>(1, P.items.size()));
     P.off_r_cycle = take(sizeof(int) * 2 * n);
     P.off_r_tiles = take(sizeof(int) * 2 * n);
-    P.off_r_ftiles = take(sizeof(int) * 2 * n);
-    P.off_r_smooth = take(sizeof(int) * 2 * n);
+    P.off_r_ftiles = take(P.mixed ? 0 : sizeof(int) * 2 * n);
+    P.off_r_smooth = take(smooth_S > 0 ? sizeof(int) * 2 * n : 0);
     P.off_io = take(sizeof(SliceIO) * n);
-    P.off_u64tab = take(sizeof(double *) * 2 * n);
-    P.off_r_p0 = take(sizeof(int) * 2 * n);
-    P.off_pitems = take(sizeof(PItem) * (size_t)std::max<long long>(1, P.n_pitems));
+    P.off_u64tab = take(P.mixed ? sizeof(double *) * 2 * n : 0);
+    // (block items, then the slice of each 64 x 16 tile when periodic)
+    P.off_bitems = take(sizeof(BItem) * (size_t)P.n_bres + sizeof(int) * (size_t)P.n_tiles);
+    P.off_ptiles = P.off_bitems + sizeof(BItem) * P.bitems.size();
     P.tables_bytes = o2;
     P.off_partf = take(sizeof(float2) * std::max(1, P.n_norm));
     P.off_partd = take(sizeof(double) * std::max<long long>(1, P.n_partd));
@@ -590,14 +596,14 @@ std::vector<char> bind_tables(const Plan &P, char *ws, const std::vector<SliceIO
             d.bshift_fine = (l == 1 && !P.mixed) ? &st_dev[s].bmean : nullptr;
             if (l + 1 < g.nlev) {
                 d.bc = arena + g.off_b[l + 1];
-                // level l+1's final iterate: buffer 1 after an up pass; the
-                // coarsest level ends its kCoarsePasses passes in buffer (passes-1)&1
-                const int fin = (l + 1 == g.nlev - 1) ? ((kCoarsePasses - 1) & 1) : 1;
+                // level l+1's final iterate: buffer 1 after an up pass, 0 after the
+                // coarsest level's one pass; a periodic level ends in buffer 0
+                const int fin = P.periodic || l + 1 == g.nlev - 1 ? 0 : 1;
                 d.ec = arena + g.off_u[l + 1][fin];
             }
         }
     }
-    std::vector<char> img(P.periodic ? P.tables_bytes : P.off_pitems, 0);
+    std::vector<char> img(P.off_ptiles + sizeof(int) * P.ptiles.size(), 0);
     // state zeroed except the per-slice constants; active = 1
     SliceState *st = reinterpret_cast<SliceState *>(img.data() + P.off_state);
     int *act = reinterpret_cast<int *>(img.data() + P.off_active);
@@ -610,13 +616,14 @@ std::vector<char> bind_tables(const Plan &P, char *ws, const std::vector<SliceIO
     if (!P.items.empty()) std::memcpy(img.data() + P.off_items, P.items.data(), sizeof(Item) * P.items.size());
     std::memcpy(img.data() + P.off_r_cycle, P.ranges_cycle.data(), sizeof(int) * 2 * P.n);
     std::memcpy(img.data() + P.off_r_tiles, P.ranges_tiles.data(), sizeof(int) * 2 * P.n);
-    std::memcpy(img.data() + P.off_r_ftiles, P.ranges_ftiles.data(), sizeof(int) * 2 * P.n);
+    if (!P.mixed) std::memcpy(img.data() + P.off_r_ftiles, P.ranges_ftiles.data(), sizeof(int) * 2 * P.n);
     if (!P.ranges_smooth.empty())
         std::memcpy(img.data() + P.off_r_smooth, P.ranges_smooth.data(), sizeof(int) * 2 * P.n);
     std::memcpy(img.data() + P.off_io, io.data(), sizeof(SliceIO) * P.n);
-    std::memcpy(img.data() + P.off_r_p0, P.ranges_p0.data(), sizeof(int) * 2 * P.n);
-    if (!P.pitems.empty())
-        std::memcpy(img.data() + P.off_pitems, P.pitems.data(), sizeof(PItem) * P.pitems.size());
+    if (!P.bitems.empty())
+        std::memcpy(img.data() + P.off_bitems, P.bitems.data(), sizeof(BItem) * P.bitems.size());
+    if (!P.ptiles.empty())
+        std::memcpy(img.data() + P.off_ptiles, P.ptiles.data(), sizeof(int) * P.ptiles.size());
     if (P.mixed) {
         double **tab = reinterpret_cast<double **>(img.data() + P.off_u64tab);
         for (int s = 0; s < P.n; ++s) {
@@ -781,8 +788,8 @@ struct Run {
     double **u64tab;
     float2 *partf;
     double *partd, *partd2, *partd3;
-    PItem *pitems;
-    int *r_p0;
+    BItem *bitems;
+    int *ptiles;
     std::vector<char> active_host;
     double tol;
     int max_cycles;
@@ -809,94 +816,88 @@ struct Run {
         partd = reinterpret_cast<double *>(ws + P.off_partd);
         partd2 = reinterpret_cast<double *>(ws + P.off_partd2);
         partd3 = reinterpret_cast<double *>(ws + P.off_partd3);
-        pitems = reinterpret_cast<PItem *>(ws + P.off_pitems);
-        r_p0 = reinterpret_cast<int *>(ws + P.off_r_p0);
+        bitems = reinterpret_cast<BItem *>(ws + P.off_bitems);
+        ptiles = reinterpret_cast<int *>(ws + P.off_ptiles);
         active_host.assign(P.n, 1);
     }
 
-    // ---- periodic boundaries
-    // launch arguments over level l's tiles (mid: only the slices that have a
-    // level below l)
-    PLaunch plaunch(int l, bool mid = false) const
+    // ---- register-block passes
+    // raw_rhs as in BlockLaunch; slot0: first partial-sum slot (level-0 residual norms)
+    gdf_status block(const BList &B, BlockKind kind, int level, int in_sel, int out_sel, bool fp64, double per_px,
+                     bool raw_rhs = false, int slot0 = 0)
     {
-        PLaunch a{};
+        if (B.count == 0) return GDF_OK;
+        BlockLaunch a{};
         a.levs = desc;
-        a.items = pitems + P.poff[l];
-        a.n_items = mid ? P.pmid[l] : P.pcnt[l];
+        a.items = bitems + B.off;
+        a.n_items = B.count;
+        a.G = B.G;
+        a.in_sel = in_sel;
+        a.out_sel = out_sel;
         a.active = active;
-        // the per-cycle norms go to their own arrays: the output pass keeps the
-        // partial sums of slices it skips in a resume round in partd
-        a.part_rr = partd2;
-        a.part_r = partd3;
-        return a;
-    }
-    gdf_status psmooth(int l, int half_sweeps, int &cur, bool zero_first, bool fp64)
-    {
-        for (int h = 0; h < half_sweeps; ++h) {
-            PLaunch a = plaunch(l);
-            a.colour = h & 1;
-            a.in_sel = cur;
-            a.out_sel = cur ^ 1;
-            a.zero_in = h == 0 && zero_first;
-            ProfScope ps(PC_COARSE, 0.0, s, capturing);
-            HIP_TRY(launch_psmooth_level(fp64, l == 0, a, s));
-            cur ^= 1;
-        }
+        a.done = capturing ? done : nullptr;
+        a.raw_rhs = raw_rhs ? 1 : 0;
+        // (the per-cycle norms go to their own arrays: the output pass keeps the
+        // partial sums of slices it skips in a resume round in partd)
+        a.part_rr = partd2 + slot0;
+        a.part_r = partd3 + slot0;
+        ProfScope ps(PC_COARSE, g_prof_on && !g_prof_fine_only ? pass_bytes(B.slice_px, per_px) : 0.0, s, capturing);
+        HIP_TRY(launch_block(kind, P.periodic, level == 0, B.sweeps, fp64, a, s));
         return GDF_OK;
     }
-    // One V-cycle with periodic boundaries: down the levels (pre-smoothing,
-    // residual restricted into the next level's right-hand side; coarse levels
-    // start from zero), then up (prolongation of the coarser iterate, post-
-    // smoothing).  Each slice's coarsest level is smoothed on the way down and
-    // on the way up.  Level 0 takes nu sweeps each way, the coarse levels
-    // coarse_sweeps; an even number of half-sweeps per cycle leaves the
-    // level-0 iterate in buffer 0.
+    // One V-cycle with periodic boundaries: down the levels (sweeps, residual
+    // restricted into the next level's right-hand side; coarse levels start from
+    // zero; buffer 0 -> 1), then up (prolongation of the coarser iterate, sweeps;
+    // buffer 1 -> 0).  Each slice's coarsest level is smoothed on the way down
+    // and on the way up.  Level 0 takes nu sweeps each way, the coarse levels
+    // coarse_sweeps; its iterate ends in buffer 0 and its residual norms in
+    // partd2 / partd3.
     gdf_status pcycle(bool fp64, bool zero)
     {
         gdf_status r;
-        int cur[kMaxLevels] = {0};
+        const double e = fp64 ? 8.0 : 4.0, ce = fp64 ? 8.0 : 2.0;
         for (int l = 0; l <= P.max_level; ++l) {
-            if ((r = psmooth(l, 2 * (l == 0 ? P.o.nu : P.o.csw), cur[l], l > 0 || zero, fp64))) return r;
-            if (l < P.max_level) {
-                PLaunch a = plaunch(l + 1);
-                a.in_sel = cur[l];
-                ProfScope ps(PC_COARSE, 0.0, s, capturing);
-                HIP_TRY(launch_prestrict_level(fp64, l == 0, a, s));
-            }
+            const double el = l == 0 ? e : ce;
+            const bool z = zero || l > 0;
+            if ((r = block(P.bmid[l], z ? BK_DOWN_ZERO : BK_DOWN, l, 0, 1, fp64, (z ? 2 : 3) * el + 0.25 * ce))) return r;
+            if ((r = block(P.blast[l], z ? BK_LAST_ZERO : BK_LAST_MID, l, 0, 1, fp64, (z ? 2 : 3) * el))) return r;
         }
         for (int l = P.max_level; l >= 0; --l) {
-            if (l < P.max_level) {
-                PLaunch a = plaunch(l, true);
-                a.in_sel = cur[l];
-                a.coarse_sel = cur[l + 1];
-                ProfScope ps(PC_COARSE, 0.0, s, capturing);
-                HIP_TRY(launch_pprolong_level(fp64, l == 0, a, s));
-            }
-            if ((r = psmooth(l, 2 * (l == 0 ? P.o.nu : P.o.csw), cur[l], false, fp64))) return r;
+            const double el = l == 0 ? e : ce;
+            if ((r = block(P.blast[l], BK_LAST, l, 1, 0, fp64, 3 * el, false, P.bmid[0].count))) return r;
+            if ((r = block(P.bmid[l], BK_UP, l, 1, 0, fp64, 3 * el + 0.25 * ce))) return r;
         }
         return GDF_OK;
     }
     // the in-loop convergence check after a cycle
-    gdf_status check_cycle(bool fp64)
+    gdf_status check_cycle()
     {
         if (!P.periodic) return finish(r_cycle, partf, nullptr, FIN_CHECK, 1);
-        PLaunch a = plaunch(0);
+        return finish(r_cycle, nullptr, partd2, FIN_CHECK, 1, partd3);
+    }
+    // launch arguments of the periodic per-pixel kernels (level-0 buffer 0)
+    PLaunch plaunch() const
+    {
+        PLaunch a{};
+        a.levs = desc;
+        a.slice_of = ptiles;
+        a.n_items = (int)P.ptiles.size();
         a.in_sel = 0;
-        HIP_TRY(launch_pnorm(fp64, a, s));
-        return finish(r_p0, nullptr, partd2, FIN_CHECK, 1, partd3);
+        a.part_rr = partd;
+        return a;
     }
 
     // algorithmic bytes of a list's pass over the slices still iterating
-    double pass_bytes(int li, double per_px) const
+    double pass_bytes(const std::vector<std::pair<int, double>> &slice_px, double per_px) const
     {
         double px = 0.0;
-        for (const auto &e : P.lists[li].slice_px)
+        for (const auto &e : slice_px)
             if (active_host[e.first]) px += e.second;
         return px * per_px;
     }
 
     gdf_status strip(int li, StripKind kind, int in_sel, int out_sel, float2 *partials, bool fp64,
-                     int cls, double per_px, bool slice_parity = false, bool raw_rhs = false)
+                     int cls, double per_px, bool slice_parity = false)
     {
         if (li < 0) return GDF_OK;
         const List &L = P.lists[li];
@@ -910,15 +911,14 @@ struct Run {
         a.active = active;
         a.done = capturing ? done : nullptr;
         a.partials = partials;
-        a.raw_rhs = raw_rhs ? 1 : 0;
         const bool timed = g_prof_on && (!g_prof_fine_only || cls == PC_FINE);
-        ProfScope ps(cls, timed ? pass_bytes(li, per_px) : 0.0, s, capturing);
+        ProfScope ps(cls, timed ? pass_bytes(L.slice_px, per_px) : 0.0, s, capturing);
         a.items = items + L.off;
         a.n_items = L.count;
         a.n_fast = L.n_fast;
         a.n_rows_in = L.n_rows_in;
         const bool sor = P.o.sor && (kind == SK_FINE || kind == SK_FINE_ZERO);
-        HIP_TRY(launch_strip(kind, L.csw, P.o.fsw, fp64, P.o.launch == GDF_LAUNCH_PERSISTENT, a, s, sor));
+        HIP_TRY(launch_strip(kind, P.o.fsw, fp64, P.o.launch == GDF_LAUNCH_PERSISTENT, a, s, sor));
         return GDF_OK;
     }
 
@@ -929,7 +929,7 @@ struct Run {
     int max_slots(const int *range) const
     {
         return range == r_cycle ? P.max_cycle : range == r_tiles ? P.max_tiles : range == r_ftiles ? P.max_ftiles
-             : range == r_smooth ? P.max_smooth : P.max_p0;
+             : P.max_smooth;
     }
     gdf_status finish(const int *range, const float2 *pf, const double *pd, int mode, int count,
                       const double *pd2 = nullptr)
@@ -949,14 +949,11 @@ struct Run {
         const bool raw = raw_rhs_l1;
         raw_rhs_l1 = false;
         for (int l = 1; l <= P.max_level; ++l) {
-            if ((r = strip(P.list_down[l], SK_DOWN, 0, 0, nullptr, fp64, PC_COARSE, 2.25 * e, false, raw && l == 1)))
-                return r;
-            if ((r = strip(P.list_coarse[l], SK_COARSE_ZERO, 0, 0, nullptr, fp64, PC_COARSE, 2 * e))) return r;
-            for (int k = 1; k < kCoarsePasses; ++k)
-                if ((r = strip(P.list_coarse[l], SK_COARSE, (k - 1) & 1, k & 1, nullptr, fp64, PC_COARSE, 3 * e))) return r;
+            if ((r = block(P.bmid[l], BK_DOWN_ZERO, l, 0, 0, fp64, 2.25 * e, raw && l == 1))) return r;
+            if ((r = block(P.blast[l], BK_LAST_ZERO, l, 0, 0, fp64, 2 * e, raw && l == 1))) return r;
         }
         for (int l = P.max_level - 1; l >= 1; --l)
-            if ((r = strip(P.list_up[l], SK_UP, 0, 1, nullptr, fp64, PC_COARSE, 3.25 * e))) return r;
+            if ((r = block(P.bmid[l], BK_UP, l, 0, 1, fp64, 3.25 * e))) return r;
         return GDF_OK;
     }
 
@@ -1025,7 +1022,7 @@ struct Run {
             HIP_TRY(launch_done(P.n, active, done, s));
             for (int k = 1; k <= (captured ? captured : max_cycles); ++k) {
                 if ((r = cycle(k, fp64, true, z && k == 1))) return r;
-                if ((r = check_cycle(fp64))) return r;
+                if ((r = check_cycle())) return r;
                 HIP_TRY(launch_done(P.n, active, done, s));
             }
             return GDF_OK;
@@ -1040,7 +1037,7 @@ struct Run {
                 if (!any) break;
             }
             if ((r = cycle(k, fp64, true, z && k == 1))) return r;
-            if ((r = check_cycle(fp64))) return r;
+            if ((r = check_cycle())) return r;
         }
         return GDF_OK;
     }
@@ -1230,9 +1227,9 @@ gdf_status mixed_iterate(Run &R, int gs_dtype, const void *gs, int go_dtype, con
     // correction in level-0 buffer 0)
     auto refine = [&]() -> hipError_t {
         ProfScope ps(PC_REFINE, 0.0, R.s, R.capturing);
-        return P.periodic ? launch_prefine(ra, R.plaunch(0), R.s) : launch_refine(ra, R.s);
+        return P.periodic ? launch_prefine(ra, R.plaunch(), R.s) : launch_refine(ra, R.s);
     };
-    const int *rr_range = P.periodic ? R.r_p0 : R.r_tiles;
+    const int *rr_range = R.r_tiles;
     HIP_TRY(refine());
     if ((r = R.finish(rr_range, nullptr, R.partd, FIN_CHECK, 0))) return r;
     const int steps = std::max(1, P.o.max_vc / P.o.inner);
@@ -1282,9 +1279,7 @@ gdf_status solve_body(Run &R, const SolveIO &x)
                 // (later rounds touch only the resumed slices: not counted)
                 ProfScope ps(PC_FINALIZE, round ? 0.0 : all_px * (2.0 * P.esz + go_b + f_b), R.s, R.capturing);
                 if (P.periodic) {
-                    PLaunch a = R.plaunch(0);
-                    a.in_sel = 0;
-                    a.part_rr = R.partd;
+                    const PLaunch a = R.plaunch();
                     HIP_TRY(launch_pfinalize(P.fp64, x.go_dtype, x.go, P.o.out_dtype, x.f, R.io, a, R.st,
                                              round ? R.only : nullptr, R.s));
                 } else {
@@ -1293,7 +1288,7 @@ gdf_status solve_body(Run &R, const SolveIO &x)
                                             R.partd, R.s));
                 }
             }
-            if ((r = R.finish(P.periodic ? R.r_p0 : (rows ? R.r_ftiles : R.r_tiles), nullptr, R.partd, FIN_FINAL, 0)))
+            if ((r = R.finish(rows && !P.periodic ? R.r_ftiles : R.r_tiles, nullptr, R.partd, FIN_FINAL, 0)))
                 return r;
             if (R.capturing) {
                 if (round == 2) break;
@@ -1450,7 +1445,7 @@ gdf_status autotuned(const std::vector<unsigned long long> &key, const gdf_solve
         if (!base.sor && base.precision != GDF_PREC_FP64)
             for (int fs : {4, 5})
                 if (fs >= 2 * cur.nu && fs <= 2 * cur.nu + 2 && (!base.fine_sweeps || base.fine_sweeps == fs))
-                    sw.push_back({fs, 1});
+                    sw.push_back({fs == 2 * cur.nu ? base.fine_sweeps : fs, 1});   // (2 nu: the default, 0)
         for (const Sweeps &w : sw)
             for (int tr : tiles) {
                 if (w.fs == cur.fine_sweeps && w.sor == cur.sor && tr == cur.tile_rows) continue;
@@ -1696,8 +1691,7 @@ static gdf_status run_captured(const std::vector<unsigned long long> &key, Run &
     hipGraphExec_t ex = graph_lookup(key);
     if (!ex) {
         if (o.launch == GDF_LAUNCH_PERSISTENT) {
-            strip_prepare(o.csw, o.fsw, R.P.fp64);
-            if (o.csw_auto) strip_prepare(o.nu, o.fsw, R.P.fp64);
+            strip_prepare(o.fsw, R.P.fp64);
         }
         R.capturing = true;
         HIP_TRY(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
@@ -1898,9 +1892,9 @@ static gdf_status fuse_stack_plain(const uint8_t *stack_all, int S_all, int H, i
         if (periodic) {
             // the norms of Eq. (1)'s right-hand side with the periodic Laplacian,
             // from the b_u the smoothing wrote and the stack
-            HIP_TRY(launch_pprep(P.fp64, P.fp64 ? GDF_F64 : GDF_F32, nullptr, GDF_U8, stack, R.io, R.plaunch(0),
+            HIP_TRY(launch_pprep(P.fp64, P.fp64 ? GDF_F64 : GDF_F32, nullptr, GDF_U8, stack, R.io, R.plaunch(),
                                  R.partd, R.partd2, R.partd3, s));
-            HIP_TRY(launch_finish_rhs(P.n, P.max_p0, R.r_p0, R.partd, R.partd2, R.partd3, R.st, s));
+            HIP_TRY(launch_finish_rhs(P.n, P.max_tiles, R.r_tiles, R.partd, R.partd2, R.partd3, R.st, s));
         } else {
             HIP_TRY(launch_finish_rhs(P.n, P.max_smooth, R.r_smooth, R.partd, R.partd2, R.partd3, R.st, s));
         }
@@ -2230,13 +2224,13 @@ static gdf_status solve_slices_plain(int n, const gdf_slice_desc *d, int gs_dtyp
         {
             ProfScope ps(PC_PREP, 0.0, s, R.capturing);
             if (P.periodic)
-                HIP_TRY(launch_pprep(P.fp64, gs_dtype, gs, go_dtype, go, R.io, R.plaunch(0), R.partd, R.partd2,
+                HIP_TRY(launch_pprep(P.fp64, gs_dtype, gs, go_dtype, go, R.io, R.plaunch(), R.partd, R.partd2,
                                      R.partd3, s));
             else
                 HIP_TRY(launch_prep(P.fp64, gs_dtype, gs, go_dtype, go, R.io, n, P.n_tiles, R.desc, R.partd,
                                     R.partd2, R.partd3, s));
         }
-        HIP_TRY(launch_finish_rhs(n, P.periodic ? P.max_p0 : P.max_tiles, P.periodic ? R.r_p0 : R.r_tiles, R.partd, R.partd2, R.partd3, R.st, s));
+        HIP_TRY(launch_finish_rhs(n, P.max_tiles, R.r_tiles, R.partd, R.partd2, R.partd3, R.st, s));
         return solve_body(R, x);
     };
 
@@ -2368,8 +2362,7 @@ static gdf_status backward_plain(int n, const gdf_slice_desc *d, int dtype, cons
     {
         ProfScope ps(PC_ADJOINT, 0.0, s, false);
         if (P.periodic) {
-            PLaunch a = R.plaunch(0);
-            a.in_sel = 0;
+            const PLaunch a = R.plaunch();
             HIP_TRY(launch_padjoint(P.fp64, gs, f, grad_gs, grad_go, R.io, n, a, R.st, P.mixed ? R.u64tab : nullptr,
                                     R.partd, s));
         } else {
@@ -2377,7 +2370,7 @@ static gdf_status backward_plain(int n, const gdf_slice_desc *d, int dtype, cons
                                             P.mixed ? R.u64tab : nullptr, R.partd, s));
         }
     }
-    if ((r = R.finish(P.periodic ? R.r_p0 : R.r_tiles, nullptr, R.partd, FIN_SUM, 0))) return r;
+    if ((r = R.finish(R.r_tiles, nullptr, R.partd, FIN_SUM, 0))) return r;
     if (grad_alpha_sum) HIP_TRY(launch_sum_aux(n, R.st, grad_alpha_sum, s));
     std::vector<SliceState> h(n);
     HIP_TRY(hipMemcpyAsync(h.data(), R.st, sizeof(SliceState) * n, hipMemcpyDeviceToHost, s));

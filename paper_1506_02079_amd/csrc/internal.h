@@ -2,88 +2,10 @@
 // gradient-domain fusion library.  Not part of the public ABI.
 #pragma once
 
-#include <hip/hip_runtime.h>
-
-#include <cstddef>
-#include <cstdint>
+#include "device.h"
+#include "smooth.h"
 
 namespace gdf {
-
-constexpr int kWave = 64;          // CDNA wavefront width
-constexpr int kStripCols = 128;    // columns covered by one wave (2 per lane)
-constexpr int kWavesPerBlock = 4;  // independent waves per workgroup
-constexpr int kMaxLevels = 16;
-constexpr int kMaxWidth = 1 << 22;  // widest slice (keeps an item's rows within 32-bit offsets)
-
-#ifdef __HIPCC__
-// Logical tile of this workgroup in a 1-D grid of nb workgroups.  The hardware
-// hands workgroup b to XCD b % 8; remapping gives each XCD a contiguous range of
-// tiles, so tiles that share halo rows and columns run on the same XCD at about
-// the same time and meet in its L2.  A tail of fewer than 8 groups keeps its
-// order.
-__device__ __forceinline__ long long xcd_tile(long long b, long long nb)
-{
-    const long long nb8 = nb >> 3;
-    if (b >= nb8 * 8) return b;
-    return (b & 7) * nb8 + (b >> 3);
-}
-
-// ------------------------------------------------------- buffer access ---
-
-// Raw buffer resource over `bytes` bytes from `base` (no stride or swizzle;
-// dword 3 selects plain dword access on this GPU family).  The address of an
-// access is base + row offset (a scalar) + lane offset; a lane offset at or
-// past `bytes` reads zero and drops a store.  So a lane is masked by its
-// offset and a whole row by a zero-sized resource, without a branch.
-typedef __amdgpu_buffer_rsrc_t Rsrc;
-__device__ __forceinline__ Rsrc make_rsrc(const void *base, unsigned bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), (short)0, (int)bytes, 0x00020000);
-}
-// a lane offset past every window (the host keeps an item's rows below 2^31 bytes)
-constexpr unsigned kNoLane = 0x80000000u;
-
-template <typename X> struct Buf;
-template <> struct Buf<unsigned short> {
-    __device__ static unsigned short ld(Rsrc r, unsigned vo, unsigned so)
-    {
-        return __builtin_amdgcn_raw_buffer_load_b16(r, (int)vo, (int)so, 0);
-    }
-    __device__ static void st(unsigned short v, Rsrc r, unsigned vo, unsigned so)
-    {
-        __builtin_amdgcn_raw_buffer_store_b16(v, r, (int)vo, (int)so, 0);
-    }
-};
-template <> struct Buf<unsigned> {
-    __device__ static unsigned ld(Rsrc r, unsigned vo, unsigned so)
-    {
-        return __builtin_amdgcn_raw_buffer_load_b32(r, (int)vo, (int)so, 0);
-    }
-    __device__ static void st(unsigned v, Rsrc r, unsigned vo, unsigned so)
-    {
-        __builtin_amdgcn_raw_buffer_store_b32(v, r, (int)vo, (int)so, 0);
-    }
-};
-template <> struct Buf<float> {
-    __device__ static float ld(Rsrc r, unsigned vo, unsigned so) { return __uint_as_float(Buf<unsigned>::ld(r, vo, so)); }
-    __device__ static void st(float v, Rsrc r, unsigned vo, unsigned so) { Buf<unsigned>::st(__float_as_uint(v), r, vo, so); }
-};
-typedef unsigned U2 __attribute__((ext_vector_type(2)));
-typedef unsigned U4 __attribute__((ext_vector_type(4)));
-template <typename X, typename R> struct BufBits {   // 8- and 16-byte values
-    __device__ static X ld(Rsrc r, unsigned vo, unsigned so)
-    {
-        if constexpr (sizeof(X) == 8) return __builtin_bit_cast(X, __builtin_amdgcn_raw_buffer_load_b64(r, (int)vo, (int)so, 0));
-        else return __builtin_bit_cast(X, __builtin_amdgcn_raw_buffer_load_b128(r, (int)vo, (int)so, 0));
-    }
-    __device__ static void st(X v, Rsrc r, unsigned vo, unsigned so)
-    {
-        if constexpr (sizeof(X) == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(R, v), r, (int)vo, (int)so, 0);
-        else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(R, v), r, (int)vo, (int)so, 0);
-    }
-};
-template <> struct Buf<double> : BufBits<double, U2> {};
-#endif  // __HIPCC__
 
 // One multigrid level of one slice.  Arrays are row-major with row pitch
 // `pitch` (elements, even, >= W + 1 for odd W) so that a lane's two-column
@@ -106,7 +28,7 @@ struct LevelDesc {
     int slice;       // slice index (flags, partial sums)
     int pad_;
     // level 1: the level-0 mean; a right-hand side restricted from the unshifted
-    // level-0 one (StripLaunch::raw_rhs) has each cell's children's share of it
+    // level-0 one (BlockLaunch::raw_rhs) has each cell's children's share of it
     // subtracted on load
     const double *bshift_fine;
 };
@@ -136,17 +58,12 @@ struct StripLaunch {
     const int *active;       // per-slice "still iterating" flags
     const int *done;         // if non-null and set: no slice is iterating (every wave exits at once)
     float2 *partials;        // per-item partial sums (r^2, r) (RES_NORM / RES_BOTH)
-    int raw_rhs;             // level 1: b holds sums of unshifted level-0 values (see LevelDesc)
 };
 
 // Strip kernel variants (template instances live in mg_kernels.hip).
 enum StripKind {
     SK_FIRST_RESTRICT,  // finest, first pass of a solve from zero: restrict b (no sweeps)
     SK_FINE,         // prolongate, fsw sweeps, residual -> norm + restrict (finest, fused up+down)
-    SK_DOWN,         // zero start, csw sweeps, restrict (coarse levels, down leg)
-    SK_UP,           // prolongate, csw sweeps (coarse levels, up leg)
-    SK_COARSE_ZERO,  // zero start, 2 sweeps (coarsest level)
-    SK_COARSE,       // 2 sweeps (coarsest level)
     SK_SINGLE_ZERO,  // zero start, 2 sweeps, residual -> norm (single-level slices)
     SK_SINGLE,       // 2 sweeps, residual -> norm
     SK_FINE_ZERO,    // as SK_FINE from a zero iterate (the first cycle after SK_FIRST_RESTRICT)
@@ -155,29 +72,28 @@ enum StripKind {
 
 // Halo (G) of a strip kind: stages after the load, plus one for prolongation,
 // rounded up to even.  Valid output width per strip is 128 - 2G.
-int strip_halo(StripKind k, int csw, int fsw);
+int strip_halo(StripKind k, int fsw);
 
 // Enqueue one strip pass (one launch).  Items [0, a.n_fast) stay clear of
 // the slice's edges (rows y0 - G .. y1 + G in [1, H - 2], columns x0 - G ..
 // x0 - G + 127 in [1, W - 2]) and run the code without row guards and edge
 // masks; items [a.n_fast, a.n_rows_in) have such rows but touch a column edge
-// (no row guards, per-lane masks); the others run the guarded code.  csw: sweeps per smoothing step of
-// the coarse passes; fsw: sweeps of the fused finest pass
-// (SK_FINE).  fp64 selects double precision.  persistent: the grid is capped
+// (no row guards, per-lane masks); the others run the guarded code.  fsw: sweeps of the fused finest
+// pass (SK_FINE).  fp64 selects double precision.  persistent: the grid is capped
 // at the workgroups resident on the device at once and each wave loops over
 // the list's items; otherwise one wave per item.  sor: the over-relaxed
 // instances of SK_FINE / SK_FINE_ZERO (FP32, fsw 4 or 5; any other pass or
 // setting is an error).
-hipError_t launch_strip(StripKind k, int csw, int fsw, bool fp64, bool persistent, const StripLaunch &a,
-                        hipStream_t s, bool sor = false);
+hipError_t launch_strip(StripKind k, int fsw, bool fp64, bool persistent, const StripLaunch &a, hipStream_t s,
+                        bool sor = false);
 
 // Waves of a strip kernel variant that the device holds at once (occupancy x
 // SIMDs); 0 if the runtime cannot tell (no device).
-int strip_resident_waves(StripKind k, int csw, int fsw, bool fp64);
+int strip_resident_waves(StripKind k, int fsw, bool fp64);
 
-// Resolves the persistent grid sizes of every strip kernel variant for nu,
+// Resolves the persistent grid sizes of every strip kernel variant for
 // fsw and the precision (device queries; call before a stream capture begins).
-void strip_prepare(int csw, int fsw, bool fp64);
+void strip_prepare(int fsw, bool fp64);
 
 // ---- per-slice reductions and flags ------------------------------------
 
@@ -313,50 +229,69 @@ hipError_t launch_finalize64(int go_dtype, const void *go, int out_dtype, void *
                              double *const *u64, const SliceState *state, const LevelDesc *levs,
                              hipStream_t s);
 
+// ---- register-block passes ---------------------------------------------------
+//
+// Passes over the coarse levels, and over every level of a periodic hierarchy
+// (block_kernels.hip): one workgroup per kBlockCols x kBlockRows region.  Along
+// a side of n cells with a halo of G, tile t of a Neumann level covers cells
+// [t (len - 2 G), + len) and owns those at least G from the region's ends, an
+// end on the slice's edge excepted; a periodic tile owns cells
+// [t (len - 2 G), (t + 1) (len - 2 G)) and its halo wraps.
+constexpr int kBlockCols = 2 * kWave, kBlockRows = 64, kBlockWaves = 8;
+struct BItem {
+    int lev;     // LevelDesc index
+    int tx, ty;  // tile along the columns and the rows
+};
+// tiles along a side of n cells
+constexpr int block_tiles(int n, int len, int G, bool periodic)
+{
+    return periodic ? (n + len - 2 * G - 1) / (len - 2 * G)
+                    : (n <= len ? 1 : 1 + (n - len + len - 2 * G - 1) / (len - 2 * G));
+}
+struct BlockLaunch {
+    const LevelDesc *levs;
+    const BItem *items;
+    int n_items;
+    int G;                 // halo of the list's tiles
+    int in_sel, out_sel;   // u buffers read and written
+    const int *active;
+    const int *done;       // as in StripLaunch
+    int raw_rhs;           // level 1: b holds sums of unshifted level-0 values (see LevelDesc)
+    double *part_rr, *part_r;   // level-0 residual: per-item sums of r^2 and r
+};
+// Sweeps per smoothing step is `sweeps` (two half-sweeps each).  Level 0 (periodic
+// only) has the arithmetic type and forms the residual norms on the way up;
+// coarse levels are stored as LevelDesc says.
+enum BlockKind {
+    BK_DOWN_ZERO,   // zero start, sweeps, restriction of the residual
+    BK_DOWN,        // sweeps, restriction (periodic level 0 after the first cycle)
+    BK_UP,          // prolongation, sweeps (level 0: residual norms)
+    BK_LAST_ZERO,   // coarsest level: zero start, sweeps (Neumann: 2 sweeps)
+    BK_LAST_MID,    // coarsest level that is level 0: sweeps
+    BK_LAST         // coarsest level: sweeps (level 0: residual norms)
+};
+// halo of a pass: cells that go stale per pass, rounded up to even
+constexpr int block_halo(int sweeps) { return 2 * sweeps + 2; }
+hipError_t launch_block(BlockKind k, bool periodic, bool level0, int sweeps, bool fp64, const BlockLaunch &a,
+                        hipStream_t s);
+
 // ---- periodic boundaries ---------------------------------------------------
 //
-// Slices with wrap-around (periodic) boundaries run a plain multigrid of their
-// own (periodic_kernels.hip): the same levels and finite-volume operators as
-// the Neumann hierarchy, with the neighbours of the first and last row and
-// column taken across the wrap, one launch per half-sweep (red-black, from one
-// buffer into the other, so cells of one colour that meet across the wrap of
-// an odd side read each other's previous values), a residual and restriction
-// pass, and a prolongation pass.  Every level is stored in the arithmetic
-// type.  Work is split into tiles of kPTileW x kPTileH cells of one level of
-// one slice (items); a list holds one level's items of every slice, slice by
-// slice, so per-slice partial sums occupy contiguous slots.
-constexpr int kPTileW = 64, kPTileH = 16;
-struct PItem {
-    int lev;     // LevelDesc index
-    int slice;   // slice index (SliceIO, flags)
-    int x0, y0;  // tile origin at that level
-};
+// Slices with wrap-around (periodic) boundaries run the levels and finite-volume
+// operators of the Neumann hierarchy with the neighbours of the first and last
+// row and column taken across the wrap (the passes above).  Level-0 iterates
+// are row-major.  The per-pixel kernels (periodic_kernels.hip) run one workgroup
+// per 64 x 16 pixel tile (SliceIO::tile_begin counts them slice by slice, so
+// per-slice partial sums occupy contiguous slots).
 struct PLaunch {
     const LevelDesc *levs;
-    const PItem *items;
-    int n_items;
-    const int *active;
-    int in_sel, out_sel;   // u buffers read and written (smoothing); the buffer used (others)
-    int colour;            // smoothing: cells with (x + y) % 2 == colour are updated
-    int zero_in;           // smoothing: the input iterate is zero (not read)
-    int coarse_sel;        // prolongation: the coarse level's buffer
-    double *part_rr, *part_r;   // level-0 residual: per-item sums of r^2 and r
+    const int *slice_of;   // the slice of each tile
+    int n_items;           // tiles
+    int in_sel;            // the level-0 buffer read
+    double *part_rr;       // per-item sums of r^2
 };
 // Buffer element types (gdf_dtype values of the public header).
 enum { GDF_DT_U8 = 0, GDF_DT_F32 = 1, GDF_DT_F64 = 2 };
-// One red-black half-sweep of a level (items of that level); level0: the
-// items are on level 0 (stored in the arithmetic type, coarse levels of an
-// FP32 hierarchy in bfloat16).
-hipError_t launch_psmooth_level(bool fp64, bool level0, const PLaunch &a, hipStream_t s);
-// residual of a level restricted into the next level's right-hand side
-// (items of the coarser level: each coarse cell sums its children's
-// residuals); from_level0: the finer level is level 0
-hipError_t launch_prestrict_level(bool fp64, bool from_level0, const PLaunch &a, hipStream_t s);
-// level-0 residual norms (r^2 and r per item; items of level 0)
-hipError_t launch_pnorm(bool fp64, const PLaunch &a, hipStream_t s);
-// u (buffer in_sel) += bilinear prolongation of the next level's iterate
-// (buffer coarse_sel); items of the finer level; into_level0: that is level 0
-hipError_t launch_pprolong_level(bool fp64, bool into_level0, const PLaunch &a, hipStream_t s);
 // b_u = alpha (g_s - g_o) into level-0 b, partials of ||alpha g_s + L g_o||^2,
 // ||b_u||^2, sum(b_u), with the periodic L; items of level 0
 hipError_t launch_pprep(bool fp64, int gs_dtype, const void *gs, int go_dtype, const void *go, const SliceIO *io,
@@ -374,55 +309,6 @@ hipError_t launch_prefine(const RefineArgs &r, const PLaunch &a, hipStream_t s);
 hipError_t launch_padjoint(bool fp64, const void *gs, const void *f, void *grad_gs, void *grad_go,
                            const SliceIO *io, int n_slices, const PLaunch &a, const SliceState *st,
                            double *const *u64, double *part_da, hipStream_t s);
-
-// ---- smoothing ------------------------------------------------------------
-
-constexpr int kSmoothWaves = 8;   // waves per smoothing workgroup (one partial-sum slot each)
-#ifndef GDF_SMOOTH_TILE_H
-#define GDF_SMOOTH_TILE_H 24
-#endif
-// smoothing tile: one workgroup per kSmoothTileW x kSmoothTileH tile of every slice
-constexpr int kSmoothTileW = 64, kSmoothTileH = GDF_SMOOTH_TILE_H;
-static_assert(kSmoothTileH % kSmoothWaves == 0, "whole rows per thread");
-
-struct SmoothArgs {
-    const uint8_t *stack;
-    long long pitch_row, pitch_slice;
-    int S, H, W;
-    int rxy, rz;
-    double wxy[8];        // in-plane taps (0..rxy)
-    double wz[16];        // cross-slice taps (0..rz)
-    double alpha;
-    float wxy_f[8];       // the same taps rounded to FP32 (FP32 kernel: kept in scalar registers)
-    float wz_f[16];
-    float alpha_f;
-    int z_lo, z_hi;       // the output slices: [z_lo, z_hi) of the S (the others only feed
-                          // their cross-slice windows); b_u, the level-1 right-hand side and
-                          // the partial sums of slice z go to index z - z_lo
-    void *gs_out;         // optional smoothed slices (contiguous [gs_zhi - gs_zlo][H][W])
-    int gs_zlo, gs_zhi;   // output slices [gs_zlo, gs_zhi) are stored into gs_out (slice z at z - gs_zlo)
-    void *b0;                 // level-0 right-hand side of slice 0 (b_u is written there);
-                              // null: neither b_u nor the partial sums are stored
-    long long b_slice_stride; // elements between consecutive slices' level-0 right-hand sides
-    int b_pitch;              // its row pitch (elements)
-    // 1 / (sum of the z taps inside the stack) for an output slice with lo
-    // taps below it and hi above it inside the stack: inv_wz[lo][hi], lo, hi <= rz
-    double inv_wz[13][13];
-    float inv_wz_f[13][13];
-    double *part_bb;      // [z_hi - z_lo][tiles] partial ||alpha g_s + L g_o||^2
-    double *part_b0;      // [z_hi - z_lo][tiles] partial ||b_u||^2
-    double *part_bs;      // [z_hi - z_lo][tiles] partial sum(b_u)
-    int tiles_x, tiles_y;
-    // optional (FP32): level-1 right-hand side (bfloat16) of slice 0, written as
-    // the sum of each coarse cell's children's b_u (no mean removed); slices are
-    // bc_slice_stride elements apart, rows bc_pitch
-    void *bc0;
-    long long bc_slice_stride;
-    int bc_pitch;
-    int robust;           // robust cross-slice averaging (FP32 only)
-};
-
-hipError_t launch_smooth(bool fp64, const SmoothArgs &a, hipStream_t s);
 
 // Transpose of the smoothing for FP32 gradients: out = K (g / D) (see
 // smooth_transpose.hip); tmp holds S H W floats, inv_d the tables 1 / Dz (S),

@@ -1,89 +1,18 @@
-// Kernels of the per-slice screened-Poisson solve of Eq. (1) with periodic
+// Kernels around the per-slice screened-Poisson solve of Eq. (1) with periodic
 // (wrap-around) boundaries: the paper's own Fourier basis (Section III-B,
 // frequency-space interpretation), where the grid Laplacian couples the
 // first and last row and column of a slice.
 //
-// The levels are those of the Neumann hierarchy (ceil-halving, sigma_l =
-// alpha 4^l, finite volumes with a narrower last column and row when a side
-// is odd).  On the torus a cell's neighbours are taken modulo the side, and
-// the coupling across a face is 2 / (width left + width right), so the faces
-// on either side of the narrower last cell carry 2 / (1 + wL).  A side of one
-// cell has no couplings (its neighbour is itself); a side of two cells couples
-// the two cells across both faces, as the pixel graph of a two-pixel ring
-// does.  Red-black Gauss-Seidel runs one launch per half-sweep, reading one
-// buffer and writing the other; where an odd side brings two cells of one
-// colour together across the wrap, each reads the other's previous value.
-// The restriction sums a coarse cell's children's residuals; the
-// prolongation is cell-centred bilinear with the neighbour taken across the
-// wrap.  Every kernel walks kPTileW x kPTileH tiles (items) with 256 threads,
-// one column each, four rows per thread; per-item partial sums are FP64.
+// These are the per-pixel passes around the multigrid, whose own passes are in
+// block_kernels.hip: right-hand side, output with its FP64 residual, mixed
+// refinement and adjoint assembly.  Every kernel walks 64 x 16 tiles
+// of level 0 with 256 threads, one column each, four rows per thread;
+// per-tile partial sums are FP64.
 #include "internal.h"
 
 namespace gdf {
 
 namespace {
-
-// a level's arrays: T on level 0, Coarse on the others (bfloat16 for FP32
-// hierarchies, as in the Neumann hierarchy)
-template <typename T> struct PStor { typedef T Coarse; };
-template <> struct PStor<float> { typedef unsigned short Coarse; };
-
-template <typename S> __device__ __forceinline__ float pget(const S *p, size_t i);
-template <> __device__ __forceinline__ float pget<float>(const float *p, size_t i) { return p[i]; }
-template <> __device__ __forceinline__ float pget<unsigned short>(const unsigned short *p, size_t i)
-{
-    return __uint_as_float((unsigned)p[i] << 16);
-}
-__device__ __forceinline__ double pget(const double *p, size_t i) { return p[i]; }
-
-__device__ __forceinline__ void pput(float *p, size_t i, float v) { p[i] = v; }
-__device__ __forceinline__ void pput(double *p, size_t i, double v) { p[i] = v; }
-__device__ __forceinline__ void pput(unsigned short *p, size_t i, float v)
-{
-    p[i] = __builtin_bit_cast(unsigned short, (__bf16)v);   // round to nearest even
-}
-
-// coupling across the face between cell i and cell (i + 1) mod n of a side of
-// n >= 2 cells whose last cell has relative width wl
-template <typename T> __device__ __forceinline__ T pface(int i, int n, T wl)
-{
-    return i >= n - 2 ? T(2) / (T(1) + wl) : T(1);
-}
-
-// The periodic finite-volume stencil of cell (y, x) of a level:
-// (A v)_p = m v_p + wy (kl (v_p - v_l) + kr (v_p - v_r)) + wx (ku (v_p - v_u) + kd (v_p - v_d))
-template <typename T> struct PSt {
-    int xl, xr, yu, yd;
-    T wx, wy, kl, kr, ku, kd, m, diag;
-};
-template <typename T> __device__ __forceinline__ PSt<T> pstencil(const LevelDesc &L, int y, int x)
-{
-    const int w = L.W, h = L.H;
-    const T wxl = (T)L.wxL, wyl = (T)L.wyL;
-    PSt<T> c;
-    c.xl = x == 0 ? w - 1 : x - 1;
-    c.xr = x == w - 1 ? 0 : x + 1;
-    c.yu = y == 0 ? h - 1 : y - 1;
-    c.yd = y == h - 1 ? 0 : y + 1;
-    c.wx = x == w - 1 ? wxl : T(1);
-    c.wy = y == h - 1 ? wyl : T(1);
-    c.kl = w > 1 ? pface<T>(c.xl, w, wxl) : T(0);
-    c.kr = w > 1 ? pface<T>(x, w, wxl) : T(0);
-    c.ku = h > 1 ? pface<T>(c.yu, h, wyl) : T(0);
-    c.kd = h > 1 ? pface<T>(y, h, wyl) : T(0);
-    c.m = (T)L.sigma * c.wx * c.wy;
-    c.diag = c.m + c.wy * (c.kl + c.kr) + c.wx * (c.ku + c.kd);
-    return c;
-}
-
-// neighbour sum wy (kl v_l + kr v_r) + wx (ku v_u + kd v_d)
-template <typename T, typename S>
-__device__ __forceinline__ T pnbr(const PSt<T> &c, const S *v, int pitch, int y, int x)
-{
-    const T h = c.kl * (T)pget(v, (size_t)y * pitch + c.xl) + c.kr * (T)pget(v, (size_t)y * pitch + c.xr);
-    const T u = c.ku * (T)pget(v, (size_t)c.yu * pitch + x) + c.kd * (T)pget(v, (size_t)c.yd * pitch + x);
-    return c.wy * h + c.wx * u;
-}
 
 __device__ double pblock_sum(double v, double *red)
 {
@@ -96,149 +25,20 @@ __device__ double pblock_sum(double v, double *red)
     return r;
 }
 
-constexpr int kPRows = kPTileH / 4;   // rows per thread
+constexpr int kPTileW = 64, kPTileH = 16, kPRows = kPTileH / 4;   // tile, rows per thread
 
-template <typename T> __device__ __forceinline__ T level0_shift(const LevelDesc &L)
+// the tile of this workgroup: its slice and origin
+struct PTile {
+    int slice, x0, y0;
+};
+__device__ __forceinline__ PTile ptile(const PLaunch &a, const SliceIO *io)
 {
-    return L.bshift ? (T)*L.bshift : T(0);
+    const int slice = a.slice_of[blockIdx.x];
+    const int lt = (int)(blockIdx.x - io[slice].tile_begin), nx = io[slice].tiles_x;
+    return PTile{slice, lt % nx * kPTileW, lt / nx * kPTileH};
 }
 
 // ---------------------------------------------------------------- kernels
-
-// One half-sweep: cells of colour a.colour take (b - shift + neighbour sum) /
-// diag from buffer in_sel, the others are copied; written to buffer out_sel.
-template <typename T, typename S>
-__global__ __launch_bounds__(256) void psmooth_kernel(PLaunch a)
-{
-    if (blockIdx.x >= (unsigned)a.n_items) return;
-    const PItem it = a.items[blockIdx.x];
-    if (!a.active[it.slice]) return;
-    const LevelDesc L = a.levs[it.lev];
-    const int x = it.x0 + (threadIdx.x & 63);
-    if (x >= L.W) return;   // (no barrier in this kernel)
-    const S *uin = static_cast<const S *>(L.u[a.in_sel]);
-    S *uout = static_cast<S *>(L.u[a.out_sel]);
-    const S *b = static_cast<const S *>(L.b);
-    const T bsh = level0_shift<T>(L);
-#pragma unroll
-    for (int i = 0; i < kPRows; ++i) {
-        const int y = it.y0 + (threadIdx.x >> 6) + 4 * i;
-        if (y >= L.H) break;
-        const size_t p = (size_t)y * L.pitch + x;
-        T v;
-        if (((x + y) & 1) == a.colour) {
-            const PSt<T> c = pstencil<T>(L, y, x);
-            const T nb = a.zero_in ? T(0) : pnbr<T>(c, uin, L.pitch, y, x);
-            v = ((T)pget(b, p) - bsh + nb) / c.diag;
-        } else {
-            v = a.zero_in ? T(0) : (T)pget(uin, p);
-        }
-        pput(uout, p, v);
-    }
-}
-
-// Coarse right-hand side: each cell of the coarser level (items of that level)
-// sums the residuals b - A u of its children on the finer level (buffer in_sel).
-template <typename T, typename SF, typename SC>
-__global__ __launch_bounds__(256) void prestrict_kernel(PLaunch a)
-{
-    if (blockIdx.x >= (unsigned)a.n_items) return;
-    const PItem it = a.items[blockIdx.x];
-    if (!a.active[it.slice]) return;
-    const LevelDesc C = a.levs[it.lev];
-    const LevelDesc F = a.levs[it.lev - 1];
-    const int X = it.x0 + (threadIdx.x & 63);
-    if (X >= C.W) return;
-    const SF *u = static_cast<const SF *>(F.u[a.in_sel]);
-    const SF *b = static_cast<const SF *>(F.b);
-    SC *bc = static_cast<SC *>(C.b);
-    const T bsh = level0_shift<T>(F);
-#pragma unroll
-    for (int i = 0; i < kPRows; ++i) {
-        const int Y = it.y0 + (threadIdx.x >> 6) + 4 * i;
-        if (Y >= C.H) break;
-        T sum = T(0);
-        for (int dy = 0; dy < 2; ++dy)
-            for (int dx = 0; dx < 2; ++dx) {
-                const int y = 2 * Y + dy, x = 2 * X + dx;
-                if (y >= F.H || x >= F.W) continue;
-                const PSt<T> c = pstencil<T>(F, y, x);
-                const T uc = (T)pget(u, (size_t)y * F.pitch + x);
-                sum += (T)pget(b, (size_t)y * F.pitch + x) - bsh - (c.diag * uc - pnbr<T>(c, u, F.pitch, y, x));
-            }
-        pput(bc, (size_t)Y * C.pitch + X, sum);
-    }
-}
-
-// Level-0 residual r = b - shift - A u (buffer in_sel) in the working
-// precision: per-item sums of r^2 and r in FP64.
-template <typename T>
-__global__ __launch_bounds__(256) void pnorm_kernel(PLaunch a)
-{
-    __shared__ double red[4];
-    if (blockIdx.x >= (unsigned)a.n_items) return;
-    const PItem it = a.items[blockIdx.x];
-    double s2 = 0.0, s1 = 0.0;
-    const bool act = a.active[it.slice] != 0;   // (uniform per block)
-    if (act) {
-        const LevelDesc L = a.levs[it.lev];
-        const int x = it.x0 + (threadIdx.x & 63);
-        const T *u = static_cast<const T *>(L.u[a.in_sel]);
-        const T *b = static_cast<const T *>(L.b);
-        const T bsh = level0_shift<T>(L);
-        if (x < L.W) {
-#pragma unroll
-            for (int i = 0; i < kPRows; ++i) {
-                const int y = it.y0 + (threadIdx.x >> 6) + 4 * i;
-                if (y >= L.H) break;
-                const PSt<T> c = pstencil<T>(L, y, x);
-                const T uc = u[(size_t)y * L.pitch + x];
-                const T r = b[(size_t)y * L.pitch + x] - bsh - (c.diag * uc - pnbr<T>(c, u, L.pitch, y, x));
-                s2 += (double)r * (double)r;
-                s1 += (double)r;
-            }
-        }
-    }
-    const double t2 = pblock_sum(s2, red), t1 = pblock_sum(s1, red);
-    if (threadIdx.x == 0) {
-        a.part_rr[blockIdx.x] = act ? t2 : 0.0;
-        a.part_r[blockIdx.x] = act ? t1 : 0.0;
-    }
-}
-
-// u (buffer in_sel) += bilinear prolongation of the coarser level's iterate
-// (buffer coarse_sel): weights 9/16 on the parent, 3/16 on the parent's
-// neighbours towards the cell in x and in y, 1/16 on the diagonal one, the
-// neighbours taken across the wrap.
-template <typename T, typename SF, typename SC>
-__global__ __launch_bounds__(256) void pprolong_kernel(PLaunch a)
-{
-    if (blockIdx.x >= (unsigned)a.n_items) return;
-    const PItem it = a.items[blockIdx.x];
-    if (!a.active[it.slice]) return;
-    const LevelDesc F = a.levs[it.lev];
-    const LevelDesc C = a.levs[it.lev + 1];
-    const int x = it.x0 + (threadIdx.x & 63);
-    if (x >= F.W) return;
-    SF *u = static_cast<SF *>(F.u[a.in_sel]);
-    const SC *e = static_cast<const SC *>(C.u[a.coarse_sel]);
-    const int X = x >> 1;
-    int Xn = (x & 1) ? X + 1 : X - 1;
-    Xn = Xn < 0 ? C.W - 1 : (Xn >= C.W ? 0 : Xn);
-#pragma unroll
-    for (int i = 0; i < kPRows; ++i) {
-        const int y = it.y0 + (threadIdx.x >> 6) + 4 * i;
-        if (y >= F.H) break;
-        const int Y = y >> 1;
-        int Yn = (y & 1) ? Y + 1 : Y - 1;
-        Yn = Yn < 0 ? C.H - 1 : (Yn >= C.H ? 0 : Yn);
-        const T e00 = (T)pget(e, (size_t)Y * C.pitch + X), e01 = (T)pget(e, (size_t)Y * C.pitch + Xn);
-        const T e10 = (T)pget(e, (size_t)Yn * C.pitch + X), e11 = (T)pget(e, (size_t)Yn * C.pitch + Xn);
-        const T v = T(0.5625) * e00 + T(0.1875) * (e01 + e10) + T(0.0625) * e11;
-        const size_t p = (size_t)y * F.pitch + x;
-        pput(u, p, (T)pget(u, p) + v);
-    }
-}
 
 template <typename V> __device__ __forceinline__ double ldd(const V *p, long long i) { return (double)p[i]; }
 
@@ -269,9 +69,9 @@ __global__ __launch_bounds__(256) void pprep_kernel(const TS *gs, const TO *go, 
 {
     __shared__ double red[4];
     if (blockIdx.x >= (unsigned)a.n_items) return;
-    const PItem it = a.items[blockIdx.x];
+    const PTile it = ptile(a, io);
     const SliceIO P = io[it.slice];
-    const LevelDesc L = a.levs[it.lev];
+    const LevelDesc L = a.levs[P.lev0];
     T *b = static_cast<T *>(L.b);
     const int x = it.x0 + (threadIdx.x & 63);
     double sbb = 0.0, sb0 = 0.0, sbs = 0.0;
@@ -314,10 +114,10 @@ __global__ __launch_bounds__(256) void pfinalize_kernel(const TO *go, TF *f, con
 {
     __shared__ double red[4];
     if (blockIdx.x >= (unsigned)a.n_items) return;
-    const PItem it = a.items[blockIdx.x];
+    const PTile it = ptile(a, io);
     if (only && !only[it.slice]) return;   // uniform per block: keeps this slice's partial sum
     const SliceIO P = io[it.slice];
-    const LevelDesc L = a.levs[it.lev];
+    const LevelDesc L = a.levs[P.lev0];
     const T *u = static_cast<const T *>(L.u[a.in_sel]);
     const T *b = static_cast<const T *>(L.b);
     const double shift = st[it.slice].shift + st[it.slice].uoff;
@@ -348,11 +148,11 @@ __global__ __launch_bounds__(256) void prefine_kernel(RefineArgs r, PLaunch a)
 {
     __shared__ double red[4];
     if (blockIdx.x >= (unsigned)a.n_items) return;
-    const PItem it = a.items[blockIdx.x];
+    const PTile it = ptile(a, r.io);
     double srr = 0.0;
     if (r.active[it.slice]) {   // uniform per block
         const SliceIO P = r.io[it.slice];
-        const LevelDesc L = a.levs[it.lev];
+        const LevelDesc L = a.levs[P.lev0];
         const long long pl = L.pitch;
         const double *uin = r.u64[r.in_sel * r.n_slices + it.slice];
         double *uout = r.u64[(r.in_sel ^ 1) * r.n_slices + it.slice];
@@ -404,9 +204,9 @@ __global__ __launch_bounds__(256) void padjoint_kernel(const T *gs, const T *f, 
 {
     __shared__ double red[4];
     if (blockIdx.x >= (unsigned)a.n_items) return;
-    const PItem it = a.items[blockIdx.x];
+    const PTile it = ptile(a, io);
     const SliceIO P = io[it.slice];
-    const LevelDesc L = a.levs[it.lev];
+    const LevelDesc L = a.levs[P.lev0];
     const TL *lam = u64 ? reinterpret_cast<const TL *>(u64[(st[it.slice].cycles & 1) * n + it.slice])
                         : static_cast<const TL *>(L.u[a.in_sel]);
     const double shift = u64 ? 0.0 : st[it.slice].shift + st[it.slice].uoff;   // constant parts of lambda
@@ -428,45 +228,9 @@ __global__ __launch_bounds__(256) void padjoint_kernel(const T *gs, const T *f, 
     if (threadIdx.x == 0) part_da[blockIdx.x] = t;
 }
 
-template <class K> hipError_t plaunch(K kernel, int n_items, hipStream_t s, const PLaunch &a)
-{
-    if (n_items <= 0) return hipSuccess;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)n_items), dim3(256), 0, s, a);
-    return hipGetLastError();
-}
-
 }  // namespace
 
 // ------------------------------------------------------------------- launch
-
-// level 0 of a list (items of level 0) has the arithmetic type; coarse levels
-// the coarse storage; a.levs[it.lev] tells which level an item is on, so each
-// list is launched with the storage of its level (fine: level 0)
-hipError_t launch_psmooth_level(bool fp64, bool level0, const PLaunch &a, hipStream_t s)
-{
-    if (fp64) return plaunch(psmooth_kernel<double, double>, a.n_items, s, a);
-    return level0 ? plaunch(psmooth_kernel<float, float>, a.n_items, s, a)
-                  : plaunch(psmooth_kernel<float, unsigned short>, a.n_items, s, a);
-}
-
-hipError_t launch_prestrict_level(bool fp64, bool from_level0, const PLaunch &a, hipStream_t s)
-{
-    if (fp64) return plaunch(prestrict_kernel<double, double, double>, a.n_items, s, a);
-    return from_level0 ? plaunch(prestrict_kernel<float, float, unsigned short>, a.n_items, s, a)
-                       : plaunch(prestrict_kernel<float, unsigned short, unsigned short>, a.n_items, s, a);
-}
-
-hipError_t launch_pprolong_level(bool fp64, bool into_level0, const PLaunch &a, hipStream_t s)
-{
-    if (fp64) return plaunch(pprolong_kernel<double, double, double>, a.n_items, s, a);
-    return into_level0 ? plaunch(pprolong_kernel<float, float, unsigned short>, a.n_items, s, a)
-                       : plaunch(pprolong_kernel<float, unsigned short, unsigned short>, a.n_items, s, a);
-}
-
-hipError_t launch_pnorm(bool fp64, const PLaunch &a, hipStream_t s)
-{
-    return fp64 ? plaunch(pnorm_kernel<double>, a.n_items, s, a) : plaunch(pnorm_kernel<float>, a.n_items, s, a);
-}
 
 hipError_t launch_pprep(bool fp64, int gs_dtype, const void *gs, int go_dtype, const void *go, const SliceIO *io,
                         const PLaunch &a, double *pbb, double *pb0, double *pbs, hipStream_t s)

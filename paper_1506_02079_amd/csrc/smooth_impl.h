@@ -18,7 +18,7 @@
 // partial sums of ||alpha I1 + L I0||^2 (the norm of Eq. (1)'s right-hand
 // side), ||b_u||^2 and sum(b_u).  The smoothed stack is written only when asked.
 #pragma once
-#include "internal.h"
+#include "smooth.h"
 
 namespace gdf {
 

@@ -1,5 +1,5 @@
 // Dispatch of the anisotropic smoothing kernel over its compile-time radii.
-#include "internal.h"
+#include "smooth.h"
 
 namespace gdf {
 
