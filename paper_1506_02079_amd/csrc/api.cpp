@@ -66,6 +66,18 @@ constexpr double kSigmaLight = 0.05;
 // An FP32 V-cycle that shrinks the residual by less than this factor (the
 // usual factor is 0.05 - 0.3) means the iterate has reached FP32's floor.
 constexpr double kStallRatio = 0.6;
+// Batches of at most this many pixels run the fused finest passes as register
+// blocks instead of marched strips (unless the caller sets the strips' rows or
+// a persistent grid).  A block has no chain of dependent rows and fills the chip
+// with a small batch, but loads and computes 1.72 cells per cell owned, a strip
+// 1.48 once there are enough items for tall ones.  Per pass of 4 sweeps: 6 x 96 x
+// 80, 28 us as strips and 11 as blocks; a training step on 16 x 1024^2 2.73 and 2.39
+// ms; 24 x 901 x 1100 1.98 and 1.89 ms a call; 33 x 1021 x 1531 1.75 and 1.73 ms; 3 x
+// 4096^2 (50 Mpx) 1.62 and 1.64 ms; 64 x 2048^2 5.35 and 5.89 ms.
+constexpr double kFineBlockPx = 4.5e7;
+// The row-marching output pass from this many waves on: below it, the march of
+// 64 rows is longer (22 us) than the whole quad pass.
+constexpr long long kFinRowsMin = 256;
 constexpr int kTileW = 64, kTileH = 16;
 constexpr size_t kAlign = 256;
 
@@ -238,6 +250,8 @@ struct Plan {
     // whose coarsest level it is (last); level 0 only when periodic
     std::vector<BItem> bitems;
     BList bmid[kMaxLevels], blast[kMaxLevels];
+    BList bfine;               // Neumann level 0, when its fused passes run as blocks
+    bool fine_blocks = false;
     long long n_bres = 0;      // items reserved in the workspace (either boundary)
     int max_level = 0;
     std::vector<int> ranges_cycle, ranges_tiles, ranges_ftiles, ranges_smooth;
@@ -377,6 +391,16 @@ void list_ranges(const Plan &P, int li, int base, std::vector<int> &r)
     }
 }
 
+// the same for `count` block items from `off` on, one slot each
+void block_ranges(const Plan &P, int off, int count, std::vector<int> &r)
+{
+    for (int i = 0; i < count; ++i) {
+        const int s = P.descs[P.bitems[off + i].lev].slice;
+        if (r[2 * s] < 0) r[2 * s] = i;
+        r[2 * s + 1] = i + 1;
+    }
+}
+
 // Builds geometry, work lists and the workspace layout.  Host only.
 gdf_status make_plan(Plan &P, int n, const std::vector<int> &H, const std::vector<int> &W,
                      const std::vector<double> &alpha, const Opts &o, int smooth_S)
@@ -445,8 +469,15 @@ gdf_status make_plan(Plan &P, int n, const std::vector<int> &H, const std::vecto
     std::vector<int> mid0, single0;
     for (int s = 0; s < n; ++s) (P.g[s].nlev > 1 ? mid0 : single0).push_back(s);
     P.list_first = add_list(P, SK_FIRST_RESTRICT, mid0);
-    P.list_fine = add_list(P, SK_FINE, mid0);
+    double px0 = 0.0;
+    for (int s : mid0) px0 += (double)H[s] * W[s];
+    P.fine_blocks = px0 <= kFineBlockPx && !o.tile_rows && o.launch == GDF_LAUNCH_GRID;
+    if (!P.fine_blocks) P.list_fine = add_list(P, SK_FINE, mid0);
     P.list_single = add_list(P, SK_SINGLE, single0);
+    auto tiles = [&](int s, int l, int G, bool per) {
+        return (long long)block_tiles(P.g[s].w[l], kBlockCols, G, per) * block_tiles(P.g[s].h[l], kBlockRows, G, per);
+    };
+    long long n_bper = 0, n_bneu = 0;
     for (int l = 0; l <= P.max_level; ++l) {
         std::vector<int> mid, last;
         for (int s = 0; s < n; ++s) {
@@ -465,14 +496,13 @@ gdf_status make_plan(Plan &P, int n, const std::vector<int> &H, const std::vecto
         }
         const int gp = block_halo(psw), gn = block_halo(nsw);
         constexpr int gl = 4;   // the Neumann coarsest level's pass: 2 sweeps, no residual
-        // (reserved for either boundary and any sweep count: the widest halo, the
-        // untrimmed periodic tiling)
+        // (counted for either boundary and any sweep count: the widest halo)
         constexpr int gmax = block_halo(3);
         for (const auto *v : {&mid, &last})
-            for (int s : *v)
-                P.n_bres += (long long)block_tiles(P.g[s].w[l], kBlockCols, gmax, true) *
-                            block_tiles(P.g[s].h[l], kBlockRows, gmax, true);
-        if (P.n_bres > 0x7fffffffLL) return set_err(GDF_EUNSUPPORTED, "problem too large for 32-bit work indices");
+            for (int s : *v) {
+                n_bper += tiles(s, l, gmax, true);
+                if (l > 0) n_bneu += tiles(s, l, gmax, false);
+            }
         if (P.periodic) {
             P.bmid[l] = add_blocks(P, l, mid, psw, gp);
             P.blast[l] = add_blocks(P, l, last, psw, gp);
@@ -481,20 +511,24 @@ gdf_status make_plan(Plan &P, int n, const std::vector<int> &H, const std::vecto
             P.blast[l] = add_blocks(P, l, last, 2, gl);
         }
     }
-    const int nC = P.list_fine >= 0 ? P.lists[P.list_fine].count : 0;
+    // level 0 as blocks (Neumann)
+    long long n_fine = 0;
+    if (P.fine_blocks) {
+        for (int s : mid0) n_fine += tiles(s, 0, block_halo(o.fsw), false);
+        if (!P.periodic) P.bfine = add_blocks(P, 0, mid0, o.fsw, block_halo(o.fsw));
+    }
+    P.n_bres = std::max(n_bper, n_fine + n_bneu);
+    if (P.n_bres > 0x7fffffffLL) return set_err(GDF_EUNSUPPORTED, "problem too large for 32-bit work indices");
+    const int nC = P.fine_blocks ? (int)n_fine : P.list_fine >= 0 ? P.lists[P.list_fine].count : 0;
     const int nS = P.list_single >= 0 ? P.lists[P.list_single].count : 0;
     P.n_norm = nC + nS;   // norm partials: fused finest pass, then single-level slices
     P.ranges_cycle.assign(2 * n, -1);
     list_ranges(P, P.list_fine, 0, P.ranges_cycle);
     list_ranges(P, P.list_single, nC, P.ranges_cycle);
+    block_ranges(P, P.bfine.off, P.bfine.count, P.ranges_cycle);
     if (P.periodic) {   // norm partials: the block items of level 0 (one level-0 list after the other)
-        P.ranges_cycle.assign(2 * n, 0);
-        const int n0 = P.bmid[0].count + P.blast[0].count;
-        for (int i = 0; i < n0; ++i) {
-            const int s = P.descs[P.bitems[P.bmid[0].off + i].lev].slice;
-            if (i == 0 || P.bitems[P.bmid[0].off + i - 1].lev != P.bitems[P.bmid[0].off + i].lev) P.ranges_cycle[2 * s] = i;
-            P.ranges_cycle[2 * s + 1] = i + 1;
-        }
+        P.ranges_cycle.assign(2 * n, -1);
+        block_ranges(P, P.bmid[0].off, P.bmid[0].count + P.blast[0].count, P.ranges_cycle);
     }
     // tiles for the per-pixel kernels
     P.io.resize(n);
@@ -845,6 +879,28 @@ struct Run {
         HIP_TRY(launch_block(kind, P.periodic, level == 0, B.sweeps, fp64, a, s));
         return GDF_OK;
     }
+    // the fused finest pass as blocks (see strip)
+    gdf_status fine_blocks(bool zero, int in_sel, int out_sel, bool slice_parity, bool fp64, double per_px)
+    {
+        if (P.bfine.count == 0) return GDF_OK;
+        BlockLaunch a{};
+        a.levs = desc;
+        a.items = bitems + P.bfine.off;
+        a.n_items = P.bfine.count;
+        a.G = P.bfine.G;
+        a.in_sel = in_sel;
+        a.out_sel = out_sel;
+        a.active = active;
+        a.done = capturing ? done : nullptr;
+        a.cycles = slice_parity ? &st[0].cycles : nullptr;
+        a.cycles_stride = (int)(sizeof(SliceState) / sizeof(int));
+        a.partials = partf;
+        const int cls = zero ? PC_FINE0 : PC_FINE;
+        const bool timed = g_prof_on && (!g_prof_fine_only || cls == PC_FINE);
+        ProfScope ps(cls, timed ? pass_bytes(P.bfine.slice_px, per_px) : 0.0, s, capturing);
+        HIP_TRY(launch_block_fine(zero, P.o.fsw, P.o.sor, fp64, a, s));
+        return GDF_OK;
+    }
     // One V-cycle with periodic boundaries: down the levels (sweeps, residual
     // restricted into the next level's right-hand side; coarse levels start from
     // zero; buffer 0 -> 1), then up (prolongation of the coarser iterate, sweeps;
@@ -962,7 +1018,7 @@ struct Run {
         if (P.periodic) return GDF_OK;   // (the first periodic cycle starts from zero)
         const double e = fp64 ? 8.0 : 4.0, ce = fp64 ? 8.0 : 2.0;
         gdf_status r;
-        const int nC = P.list_fine >= 0 ? P.lists[P.list_fine].count : 0;
+        const int nC = P.fine_blocks ? P.bfine.count : P.list_fine >= 0 ? P.lists[P.list_fine].count : 0;
         // read b, write the coarse right-hand side (a quarter per pixel), unless
         // the smoothing pass wrote it
         if (!raw_rhs_l1)
@@ -980,11 +1036,12 @@ struct Run {
         const double e = fp64 ? 8.0 : 4.0, ce = fp64 ? 8.0 : 2.0;
         gdf_status r;
         if ((r = coarse(fp64))) return r;
-        const int nC = P.list_fine >= 0 ? P.lists[P.list_fine].count : 0;
+        const int nC = P.fine_blocks ? P.bfine.count : P.list_fine >= 0 ? P.lists[P.list_fine].count : 0;
         // read b and the black half of u (the red half is dead: the first
         // half-sweep overwrites it unread; none of u when zero), write u; read
         // the coarse correction and write the coarse right-hand side (a quarter
         // per pixel each)
+        if ((r = fine_blocks(zero, (k - 1) & 1, k & 1, slice_par, fp64, (zero ? 2.0 : 2.5) * e + 0.5 * ce))) return r;
         if ((r = strip(P.list_fine, zero ? SK_FINE_ZERO : SK_FINE, (k - 1) & 1, k & 1, partf, fp64,
                        zero ? PC_FINE0 : PC_FINE, (zero ? 2.0 : 2.5) * e + 0.5 * ce, slice_par)))
             return r;
@@ -1267,7 +1324,7 @@ gdf_status solve_body(Run &R, const SolveIO &x)
     for (int i = 0; i < P.n; ++i) all_px += (double)P.g[i].H * P.g[i].W;
     // the row-marching output pass reads g_o and writes f four elements at a time
     const size_t go_e = x.go_dtype == GDF_U8 ? 1 : (x.go_dtype == GDF_F32 ? 4 : 8);
-    const bool rows = x.rows_ok && (reinterpret_cast<uintptr_t>(x.go) % (4 * go_e)) == 0 &&
+    const bool rows = x.rows_ok && P.n_ftiles >= kFinRowsMin && (reinterpret_cast<uintptr_t>(x.go) % (4 * go_e)) == 0 &&
                       (reinterpret_cast<uintptr_t>(x.f) % (size_t)(4 * f_b)) == 0;
     if (!P.mixed) {
         // rounds after the first resume slices whose exact residual missed tol

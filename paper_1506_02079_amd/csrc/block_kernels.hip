@@ -1,5 +1,5 @@
-// Register-block multigrid passes: the coarse levels of the Neumann hierarchy
-// and every level of the periodic one.
+// Register-block multigrid passes: the coarse levels of the Neumann hierarchy,
+// its finest level for small batches, and every level of the periodic one.
 //
 // A workgroup of 8 waves holds a region of 128 columns x 64 rows of one level
 // of one slice in registers: two adjacent columns per lane, 8 consecutive rows
@@ -111,8 +111,8 @@ __device__ __forceinline__ void side_coef(int i, int n, T wl, T ke, T &w, T &kl,
 
 // PLAIN: both segments are plain (one stencil for every cell); otherwise
 // coefficients are per lane and per row.
-template <typename T, typename SO, typename SC, bool PER, bool PROLONG, bool ZERO, int NHS, int RMODE,
-          bool PLAIN>
+template <typename T, typename SO, typename SC, bool PER, bool RB, bool PROLONG, bool ZERO, int NHS, int RMODE,
+          bool SOR, bool PLAIN>
 __device__ __forceinline__ void block_item(const BlockLaunch &a, const LevelDesc &L, const Seg &sx, const Seg &sy, int slot,
                                            BlockShared<T> &sh)
 {
@@ -156,7 +156,14 @@ __device__ __forceinline__ void block_item(const BlockLaunch &a, const LevelDesc
 
     // ---- loads: all rows at once
     const GDF_G SO *gb = (const GDF_G SO *)L.b;
-    const GDF_G SO *gu = (const GDF_G SO *)(a.in_sel ? L.u[1] : L.u[0]);
+    int in_sel = a.in_sel, out_sel = a.out_sel;
+    if constexpr (RB) {   // per-slice parity: the latest iterate sits in buffer cycles & 1
+        if (a.cycles) {
+            in_sel = uniform(a.cycles[(size_t)L.slice * a.cycles_stride]) & 1;
+            out_sel = in_sel ^ 1;
+        }
+    }
+    const GDF_G SO *gu = (const GDF_G SO *)(in_sel ? L.u[1] : L.u[0]);
     const bool pairs = regular || !(W & 1);   // the two columns are adjacent and start even
     auto load_rows = [&](const GDF_G SO *g, T v[R][2]) {
         if (pairs) {
@@ -178,10 +185,20 @@ __device__ __forceinline__ void block_item(const BlockLaunch &a, const LevelDesc
     };
     T b[R][2], u[R][2];
     load_rows(gb, b);
-    if constexpr (!ZERO) load_rows(gu, u);
-    else
+    if constexpr (!ZERO && RB) {
+        // rows stored by colour (LevelDesc): the lane's black pixel is element
+        // x0 / 2 of half 1; the red one is dead (the first half-sweep overwrites it)
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            u[r][(r & 1) ^ 1] = (T)ld<SO>(gu, (size_t)yw[r] * pitch + (pitch >> 1), (unsigned)x0 >> 1);
+            u[r][r & 1] = T(0);
+        }
+    } else if constexpr (!ZERO) {
+        load_rows(gu, u);
+    } else {
 #pragma unroll
         for (int r = 0; r < R; ++r) u[r][0] = u[r][1] = T(0);
+    }
 
     // ---- prolongation: cell-centred bilinear, 3/4 of the parent row plus 1/4 of
     // the next coarse row towards the fine row, then the same in x
@@ -352,7 +369,10 @@ __device__ __forceinline__ void block_item(const BlockLaunch &a, const LevelDesc
                     const T vd = r < R - 1 ? u[r < R - 1 ? r + 1 : r][j] : dn[j];
                     const T vl = j == 0 ? wave_shr1(u[r][1]) : u[r][0];
                     const T vr = j == 0 ? u[r][1] : wave_shl1(u[r][0]);
-                    u[r][j] = row(r, j, vl, vr, vu, vd);
+                    const T v = row(r, j, vl, vr, vu, vd);
+                    // SOR: every half-sweep after the first moves its cells by kOmega
+                    // times the Gauss-Seidel step (the first overwrites dead values)
+                    u[r][j] = SOR && s > 1 ? fma(T(kOmega), v - u[r][j], u[r][j]) : v;
                 }
             };
             if constexpr (PLAIN) {
@@ -389,12 +409,17 @@ __device__ __forceinline__ void block_item(const BlockLaunch &a, const LevelDesc
     // ---- store the owned cells
     const bool own = c0 >= sx.o0 && c0 < sx.o1;
     {
-        GDF_G SO *go = (GDF_G SO *)(a.out_sel ? L.u[1] : L.u[0]);
+        GDF_G SO *go = (GDF_G SO *)(out_sel ? L.u[1] : L.u[0]);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const int y = y0 + r;
             // (the pair's second column may lie in the row padding)
-            if (y >= sy.o0 && y < sy.o1 && own)
+            if constexpr (RB) {
+                if (y >= sy.o0 && y < sy.o1 && own) {   // column c0 has colour y & 1 = r & 1
+                    st<SO>(u[r][r & 1], go, (size_t)y * pitch, (unsigned)c0 >> 1);
+                    st<SO>(u[r][(r & 1) ^ 1], go, (size_t)y * pitch + (pitch >> 1), (unsigned)c0 >> 1);
+                }
+            } else if (y >= sy.o0 && y < sy.o1 && own)
                 st<PO>(SOt::pair(u[r][0], u[r][1]), go, (size_t)y * pitch, (unsigned)c0);
         }
     }
@@ -478,14 +503,19 @@ __device__ __forceinline__ void block_item(const BlockLaunch &a, const LevelDesc
                     t2 += sh.red[w][0];
                     t1 += sh.red[w][1];
                 }
-                a.part_rr[slot] = t2;
-                a.part_r[slot] = t1;
+                if constexpr (RB) {
+                    a.partials[slot] = make_float2((float)t2, (float)t1);
+                } else {
+                    a.part_rr[slot] = t2;
+                    a.part_r[slot] = t1;
+                }
             }
         }
     }
 }
 
-template <typename T, typename SO, typename SC, bool PER, bool PROLONG, bool ZERO, int NHS, int RMODE>
+template <typename T, typename SO, typename SC, bool PER, bool RB, bool PROLONG, bool ZERO, int NHS, int RMODE,
+          bool SOR = false>
 __global__ __launch_bounds__(kBlockWaves *kWave, sizeof(T) == 4 ? 4 : 2) void block_kernel(BlockLaunch a)
 {
     __shared__ BlockShared<T> sh;
@@ -494,15 +524,18 @@ __global__ __launch_bounds__(kBlockWaves *kWave, sizeof(T) == 4 ? 4 : 2) void bl
     const BItem &g = a.items[slot];
     const LevelDesc L = uniform_level(a.levs[uniform(g.lev)]);
     if (!uniform(a.active[L.slice])) {
-        if ((RMODE & RES_NORM) && threadIdx.x == 0) a.part_rr[slot] = a.part_r[slot] = 0.0;
+        if ((RMODE & RES_NORM) && threadIdx.x == 0) {
+            if constexpr (RB) a.partials[slot] = make_float2(0.f, 0.f);
+            else a.part_rr[slot] = a.part_r[slot] = 0.0;
+        }
         return;
     }
     const Seg sx = segment(PER, uniform(g.tx), L.W, kBlockCols, a.G, L.wxL);
     const Seg sy = segment(PER, uniform(g.ty), L.H, kBlockRows, a.G, L.wyL);
     if (sx.plain && sy.plain)
-        block_item<T, SO, SC, PER, PROLONG, ZERO, NHS, RMODE, true>(a, L, sx, sy, slot, sh);
+        block_item<T, SO, SC, PER, RB, PROLONG, ZERO, NHS, RMODE, SOR, true>(a, L, sx, sy, slot, sh);
     else
-        block_item<T, SO, SC, PER, PROLONG, ZERO, NHS, RMODE, false>(a, L, sx, sy, slot, sh);
+        block_item<T, SO, SC, PER, RB, PROLONG, ZERO, NHS, RMODE, SOR, false>(a, L, sx, sy, slot, sh);
 }
 
 template <typename T, bool LEVEL0, bool PER, bool PROLONG, bool ZERO, int NHS, int RMODE>
@@ -512,7 +545,7 @@ hipError_t block_go(const BlockLaunch &a, hipStream_t s)
     typedef typename std::conditional<LEVEL0, T, SC>::type SO;
     if (a.n_items <= 0) return hipSuccess;
     const dim3 g((unsigned)a.n_items), blk(kBlockWaves * kWave);
-    hipLaunchKernelGGL((block_kernel<T, SO, SC, PER, PROLONG, ZERO, NHS, RMODE>), g, blk, 0, s, a);
+    hipLaunchKernelGGL((block_kernel<T, SO, SC, PER, false, PROLONG, ZERO, NHS, RMODE>), g, blk, 0, s, a);
     return hipGetLastError();
 }
 
@@ -525,6 +558,37 @@ hipError_t block_sw(int sweeps, const BlockLaunch &a, hipStream_t s)
     case 2: return block_go<T, LEVEL0, PER, PROLONG, ZERO, 4, RMODE>(a, s);
     case 3:
         if constexpr (!LEVEL0) return block_go<T, LEVEL0, PER, PROLONG, ZERO, 6, RMODE>(a, s);
+    default: return hipErrorInvalidValue;
+    }
+}
+
+// The fused finest pass of the Neumann hierarchy: prolongation, `sweeps` sweeps,
+// residual with norms and restriction.
+template <typename T, bool ZERO, int NHS, bool SOR>
+hipError_t fine_go(const BlockLaunch &a, hipStream_t s)
+{
+    typedef typename LevelStor<T>::Coarse SC;
+    if (a.n_items <= 0) return hipSuccess;
+    hipLaunchKernelGGL((block_kernel<T, T, SC, false, true, true, ZERO, NHS, RES_BOTH, SOR>), dim3((unsigned)a.n_items),
+                       dim3(kBlockWaves * kWave), 0, s, a);
+    return hipGetLastError();
+}
+template <typename T, bool ZERO>
+hipError_t fine_sw(int sweeps, bool sor, const BlockLaunch &a, hipStream_t s)
+{
+    if (sor) {
+        if constexpr (sizeof(T) == 4) {
+            if (sweeps == 4) return fine_go<T, ZERO, 8, true>(a, s);
+            if (sweeps == 5) return fine_go<T, ZERO, 10, true>(a, s);
+        }
+        return hipErrorInvalidValue;
+    }
+    switch (sweeps) {
+    case 2: return fine_go<T, ZERO, 4, false>(a, s);
+    case 3: return fine_go<T, ZERO, 6, false>(a, s);
+    case 4: return fine_go<T, ZERO, 8, false>(a, s);
+    case 5: return fine_go<T, ZERO, 10, false>(a, s);
+    case 6: return fine_go<T, ZERO, 12, false>(a, s);
     default: return hipErrorInvalidValue;
     }
 }
@@ -571,6 +635,12 @@ hipError_t block_t(BlockKind k, bool periodic, bool level0, int sweeps, const Bl
 // half-sweep over memory), 12 x 1024 x 1200: 8.0 -> 0.55 ms a call.  Regions of
 // 128 rows (16 per wave; less halo, 120 registers) were slower on every stack
 // but the largest, and there not faster.
+hipError_t launch_block_fine(bool zero, int sweeps, bool sor, bool fp64, const BlockLaunch &a, hipStream_t s)
+{
+    if (fp64) return zero ? fine_sw<double, true>(sweeps, sor, a, s) : fine_sw<double, false>(sweeps, sor, a, s);
+    return zero ? fine_sw<float, true>(sweeps, sor, a, s) : fine_sw<float, false>(sweeps, sor, a, s);
+}
+
 hipError_t launch_block(BlockKind k, bool periodic, bool level0, int sweeps, bool fp64, const BlockLaunch &a,
                         hipStream_t s)
 {

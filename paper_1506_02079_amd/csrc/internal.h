@@ -231,8 +231,8 @@ hipError_t launch_finalize64(int go_dtype, const void *go, int out_dtype, void *
 
 // ---- register-block passes ---------------------------------------------------
 //
-// Passes over the coarse levels, and over every level of a periodic hierarchy
-// (block_kernels.hip): one workgroup per kBlockCols x kBlockRows region.  Along
+// Passes over the coarse levels, over the finest level of small batches and over
+// every level of a periodic hierarchy (block_kernels.hip): one workgroup per kBlockCols x kBlockRows region.  Along
 // a side of n cells with a halo of G, tile t of a Neumann level covers cells
 // [t (len - 2 G), + len) and owns those at least G from the region's ends, an
 // end on the slice's edge excepted; a periodic tile owns cells
@@ -258,6 +258,10 @@ struct BlockLaunch {
     const int *done;       // as in StripLaunch
     int raw_rhs;           // level 1: b holds sums of unshifted level-0 values (see LevelDesc)
     double *part_rr, *part_r;   // level-0 residual: per-item sums of r^2 and r
+    // fused finest pass of the Neumann hierarchy: as in StripLaunch
+    const int *cycles;
+    int cycles_stride;
+    float2 *partials;
 };
 // Sweeps per smoothing step is `sweeps` (two half-sweeps each).  Level 0 (periodic
 // only) has the arithmetic type and forms the residual norms on the way up;
@@ -272,6 +276,9 @@ enum BlockKind {
 };
 // halo of a pass: cells that go stale per pass, rounded up to even
 constexpr int block_halo(int sweeps) { return 2 * sweeps + 2; }
+// The fused finest pass (SK_FINE, SK_FINE_ZERO when zero) as blocks; halo
+// block_halo(sweeps).
+hipError_t launch_block_fine(bool zero, int sweeps, bool sor, bool fp64, const BlockLaunch &a, hipStream_t s);
 hipError_t launch_block(BlockKind k, bool periodic, bool level0, int sweeps, bool fp64, const BlockLaunch &a,
                         hipStream_t s);
 

@@ -44,10 +44,6 @@ __device__ __forceinline__ int xcd_logical_block()
 
 // ------------------------------------------------------------ strip pass ---
 
-// Over-relaxation factor of the SOR instances of the fused finest pass
-// (red-black order, level 0 only)
-constexpr double kOmega = 1.2;
-
 // length of the load queue for a register ring of rs rows (a divisor of rs, so
 // that queue slots are compile-time constants in the unrolled ring loop)
 #ifndef GDF_QUEUE_MAX

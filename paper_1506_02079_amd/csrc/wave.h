@@ -5,6 +5,10 @@
 
 namespace gdf {
 
+// Over-relaxation factor of the SOR instances of the fused finest pass
+// (red-black order, level 0 only)
+constexpr double kOmega = 1.2;
+
 // ------------------------------------------------------------------ DPP ---
 
 // lane i receives lane i-1's value (lane 0 receives 0)
