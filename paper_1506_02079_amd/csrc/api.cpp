@@ -78,6 +78,12 @@ constexpr double kFineBlockPx = 4.5e7;
 // The row-marching output pass from this many waves on: below it, the march of
 // 64 rows is longer (22 us) than the whole quad pass.
 constexpr long long kFinRowsMin = 256;
+// Cycles (mixed precision: refinement steps) a graph holds when the host waits for
+// the report anyway and can go on from there.  A graph cannot leave early, so
+// every cycle past the last one needed still launches its passes, each exiting at
+// once: on 96 slices of 512 to 4096 a side, which take 4 to 5 cycles, a graph of all
+// 40 took 14.0 ms and one of 6 takes 11.5 ms (10.5 with the marched prep pass).
+constexpr int kGraphCycles = 6, kGraphSteps = 3;
 constexpr int kTileW = 64, kTileH = 16;
 constexpr size_t kAlign = 256;
 
@@ -593,7 +599,7 @@ gdf_status make_plan(Plan &P, int n, const std::vector<int> &H, const std::vecto
     P.off_items = take(sizeof(Item) * std::max<size_t>(1, P.items.size()));
     P.off_r_cycle = take(sizeof(int) * 2 * n);
     P.off_r_tiles = take(sizeof(int) * 2 * n);
-    P.off_r_ftiles = take(P.mixed ? 0 : sizeof(int) * 2 * n);
+    P.off_r_ftiles = take(sizeof(int) * 2 * n);
     P.off_r_smooth = take(smooth_S > 0 ? sizeof(int) * 2 * n : 0);
     P.off_io = take(sizeof(SliceIO) * n);
     P.off_u64tab = take(P.mixed ? sizeof(double *) * 2 * n : 0);
@@ -650,7 +656,7 @@ std::vector<char> bind_tables(const Plan &P, char *ws, const std::vector<SliceIO
     if (!P.items.empty()) std::memcpy(img.data() + P.off_items, P.items.data(), sizeof(Item) * P.items.size());
     std::memcpy(img.data() + P.off_r_cycle, P.ranges_cycle.data(), sizeof(int) * 2 * P.n);
     std::memcpy(img.data() + P.off_r_tiles, P.ranges_tiles.data(), sizeof(int) * 2 * P.n);
-    if (!P.mixed) std::memcpy(img.data() + P.off_r_ftiles, P.ranges_ftiles.data(), sizeof(int) * 2 * P.n);
+    std::memcpy(img.data() + P.off_r_ftiles, P.ranges_ftiles.data(), sizeof(int) * 2 * P.n);
     if (!P.ranges_smooth.empty())
         std::memcpy(img.data() + P.off_r_smooth, P.ranges_smooth.data(), sizeof(int) * 2 * P.n);
     std::memcpy(img.data() + P.off_io, io.data(), sizeof(SliceIO) * P.n);
@@ -1067,6 +1073,17 @@ struct Run {
     // cycle).  With first = false, continues from the current iterates.  A
     // captured schedule has no host checks: it holds `captured` cycles, which
     // frozen slices skip on the device.
+    // Slices still iterating after a graph that holds too few cycles for them:
+    // marks their outputs to be formed again.
+    gdf_status still_active(bool &any)
+    {
+        gdf_status r;
+        if ((r = read_active(any))) return r;
+        if (!any) return GDF_OK;
+        HIP_TRY(hipMemcpyAsync(only, active, sizeof(int) * P.n, hipMemcpyDeviceToDevice, s));
+        return GDF_OK;
+    }
+
     gdf_status iterate(bool fp64, bool first = true, int captured = 0)
     {
         gdf_status r;
@@ -1241,15 +1258,18 @@ struct SolveIO {
     int gs_dtype, go_dtype;
     const void *gs, *go;
     void *f;
-    bool rows_ok;   // widths and g_o / f offsets fit the row-marching output pass
+    // ||b||^2 partial sums of the prepared right-hand side (mixed)
+    const int *range_b = nullptr;
+    const double *part_b = nullptr;
 };
 
-// Every width a multiple of 4 and every g_o / f row start on a four-element
-// boundary (the row-marching output pass moves four elements per lane).
-static bool fin_rows_ok(const std::vector<SliceIO> &io)
+// The row-marching passes take batches large enough for them whose slices are
+// all at least four pixels wide.
+static bool march_rows(const Plan &P)
 {
-    for (const SliceIO &v : io)
-        if ((v.W & 3) || (v.off_go & 3) || (v.pitch_go & 3) || (v.off_f & 3) || (v.pitch_f & 3)) return false;
+    if (P.n_ftiles < kFinRowsMin) return false;
+    for (const SliceGeom &g : P.g)
+        if (g.W < 4) return false;
     return true;
 }
 
@@ -1259,8 +1279,13 @@ static bool fin_rows_ok(const std::vector<SliceIO> &io)
 // u64 += e and the FP64 residual is formed again, until every slice's FP64
 // relative residual meets tol.  The right-hand side is alpha (g_s - g_o), or
 // `rhs` when given (the adjoint system).
+// The residual of the zero iterate is the right-hand side itself, which is in the
+// level-0 array already; part_b (over range_b) holds the partial sums of its
+// squares.  (Forming it again took a pass of 17 bytes per pixel, and the next one
+// 8 more to read the zeros: 5.5 ms together on 2 x 21504 x 26624.)
+// Steps k0 .. k1 of max_vcycles / inner_cycles (k1 0: all that are left).
 gdf_status mixed_iterate(Run &R, int gs_dtype, const void *gs, int go_dtype, const void *go,
-                         const void *rhs)
+                         const void *rhs, const int *range_b, const double *part_b, int k0 = 1, int k1 = 0)
 {
     const Plan &P = R.P;
     gdf_status r;
@@ -1287,12 +1312,11 @@ gdf_status mixed_iterate(Run &R, int gs_dtype, const void *gs, int go_dtype, con
         return P.periodic ? launch_prefine(ra, R.plaunch(), R.s) : launch_refine(ra, R.s);
     };
     const int *rr_range = R.r_tiles;
-    HIP_TRY(refine());
-    if ((r = R.finish(rr_range, nullptr, R.partd, FIN_CHECK, 0))) return r;
     const int steps = std::max(1, P.o.max_vc / P.o.inner);
+    if (k0 == 1 && (r = R.finish(range_b, nullptr, part_b, FIN_CHECK, 0))) return r;
     const int saved_max = R.max_cycles;
     R.max_cycles = steps;
-    for (int k = 1; k <= steps; ++k) {
+    for (int k = k0; k <= (k1 ? std::min(k1, steps) : steps); ++k) {
         if (!R.capturing) {
             bool any = true;
             if ((r = R.read_active(any))) return r;
@@ -1301,7 +1325,7 @@ gdf_status mixed_iterate(Run &R, int gs_dtype, const void *gs, int go_dtype, con
         if ((r = R.first_pass(false))) return r;
         for (int c = 1; c <= P.o.inner; ++c)
             if ((r = R.cycle(c, false, false, c == 1))) return r;
-        ra.first = 0;
+        ra.first = k == 1;
         ra.in_sel = (k - 1) & 1;
         ra.e_sel = P.periodic ? 0 : P.o.inner & 1;
         HIP_TRY(refine());
@@ -1312,7 +1336,10 @@ gdf_status mixed_iterate(Run &R, int gs_dtype, const void *gs, int go_dtype, con
 }
 
 // Prepared right-hand side (prep kernel or smoothing) -> iterate -> output.
-gdf_status solve_body(Run &R, const SolveIO &x)
+// BODY_SHORT (captured): kGraphCycles cycles, output, and no rounds after it;
+// BODY_REST then takes the solve from there to its end on the host's schedule.
+enum BodyPart { BODY_ALL, BODY_SHORT, BODY_REST };
+gdf_status solve_body(Run &R, const SolveIO &x, BodyPart part = BODY_ALL)
 {
     const Plan &P = R.P;
     gdf_status r;
@@ -1322,31 +1349,34 @@ gdf_status solve_body(Run &R, const SolveIO &x)
     const double f_b = P.o.out_dtype == GDF_F64 ? 8.0 : 4.0;
     double all_px = 0.0;
     for (int i = 0; i < P.n; ++i) all_px += (double)P.g[i].H * P.g[i].W;
-    // the row-marching output pass reads g_o and writes f four elements at a time
-    const size_t go_e = x.go_dtype == GDF_U8 ? 1 : (x.go_dtype == GDF_F32 ? 4 : 8);
-    const bool rows = x.rows_ok && P.n_ftiles >= kFinRowsMin && (reinterpret_cast<uintptr_t>(x.go) % (4 * go_e)) == 0 &&
-                      (reinterpret_cast<uintptr_t>(x.f) % (size_t)(4 * f_b)) == 0;
+    const bool rows = march_rows(P);
     if (!P.mixed) {
         // rounds after the first resume slices whose exact residual missed tol
         // (decided on the host, or on the device inside a captured graph, which
         // holds two such rounds of two cycles each)
         for (int round = 0; round < 4; ++round) {
-            if ((r = R.iterate(P.fp64, round == 0, round ? 2 : 0))) return r;
-            {
+            bool rest = true;
+            if (part == BODY_REST && round == 0 && (r = R.still_active(rest))) return r;
+            const bool again_only = round || part == BODY_REST;   // (some slices' outputs stand)
+            if (rest) {
+                if ((r = R.iterate(P.fp64, !again_only, part == BODY_SHORT ? kGraphCycles : round ? 2 : 0))) return r;
                 // (later rounds touch only the resumed slices: not counted)
-                ProfScope ps(PC_FINALIZE, round ? 0.0 : all_px * (2.0 * P.esz + go_b + f_b), R.s, R.capturing);
+                ProfScope ps(PC_FINALIZE, again_only ? 0.0 : all_px * (2.0 * P.esz + go_b + f_b), R.s, R.capturing);
                 if (P.periodic) {
                     const PLaunch a = R.plaunch();
                     HIP_TRY(launch_pfinalize(P.fp64, x.go_dtype, x.go, P.o.out_dtype, x.f, R.io, a, R.st,
-                                             round ? R.only : nullptr, R.s));
+                                             again_only ? R.only : nullptr, R.s));
                 } else {
                     HIP_TRY(launch_finalize(P.fp64, rows, x.go_dtype, x.go, P.o.out_dtype, x.f, R.io, P.n,
-                                            rows ? P.n_ftiles : P.n_tiles, R.desc, R.st, round ? R.only : nullptr,
+                                            rows ? P.n_ftiles : P.n_tiles, R.desc, R.st, again_only ? R.only : nullptr,
                                             R.partd, R.s));
                 }
             }
-            if ((r = R.finish(rows && !P.periodic ? R.r_ftiles : R.r_tiles, nullptr, R.partd, FIN_FINAL, 0)))
+            // (BODY_SHORT: a slice still iterating keeps its in-loop state)
+            if (rest && (r = R.finish(rows && !P.periodic ? R.r_ftiles : R.r_tiles, nullptr, R.partd, FIN_FINAL,
+                                      part == BODY_SHORT)))
                 return r;
+            if (part == BODY_SHORT) break;
             if (R.capturing) {
                 if (round == 2) break;
                 HIP_TRY(launch_resume_flags(P.n, R.st, R.tol, R.max_cycles, R.active, R.only, R.s));
@@ -1358,8 +1388,15 @@ gdf_status solve_body(Run &R, const SolveIO &x)
         }
         return GDF_OK;
     }
-    gdf_status q;
-    if ((q = mixed_iterate(R, x.gs_dtype, x.gs, x.go_dtype, x.go, nullptr))) return q;
+    if (part == BODY_REST) {
+        bool rest = false;
+        if ((r = R.read_active(rest))) return r;
+        if (!rest) return GDF_OK;
+        if ((r = mixed_iterate(R, x.gs_dtype, x.gs, x.go_dtype, x.go, nullptr, nullptr, nullptr, kGraphSteps + 1))) return r;
+    } else if ((r = mixed_iterate(R, x.gs_dtype, x.gs, x.go_dtype, x.go, nullptr, x.range_b, x.part_b, 1,
+                                  part == BODY_SHORT ? kGraphSteps : 0))) {
+        return r;
+    }
     {
         ProfScope ps(PC_FINALIZE, all_px * (8.0 + go_b + f_b), R.s, R.capturing);
         HIP_TRY(launch_finalize64(x.go_dtype, x.go, P.o.out_dtype, x.f, R.io, P.n, P.n_tiles,
@@ -1740,7 +1777,7 @@ gdf_status smooth_transpose(const float *grad_dev, int S, int H, int W, double s
 // Runs body (the whole device schedule of a call) as a graph: captured on
 // the stream the first time for this key (sizes, pointers, stream and
 // options), then replayed.  Convergence is decided on the device inside the
-// graph (per-slice flags); the host reads the states once, afterwards.
+// graph (per-slice flags); an asynchronous call's graph holds the whole schedule.
 static gdf_status run_captured(const std::vector<unsigned long long> &key, Run &R, const Opts &o,
                                const std::function<gdf_status()> &body)
 {
@@ -1936,7 +1973,8 @@ static gdf_status fuse_stack_plain(const uint8_t *stack_all, int S_all, int H, i
     x.go_dtype = GDF_U8;
     x.go = stack;
     x.f = f;
-    x.rows_ok = fin_rows_ok(io);
+    x.range_b = periodic ? R.r_tiles : R.r_smooth;
+    x.part_b = R.partd2;
 
     auto body = [&]() -> gdf_status {
         {
@@ -1955,7 +1993,7 @@ static gdf_status fuse_stack_plain(const uint8_t *stack_all, int S_all, int H, i
         } else {
             HIP_TRY(launch_finish_rhs(P.n, P.max_smooth, R.r_smooth, R.partd, R.partd2, R.partd3, R.st, s));
         }
-        return solve_body(R, x);
+        return solve_body(R, x, o.use_graph && report ? BODY_SHORT : BODY_ALL);
     };
     if (!o.use_graph) {
         if ((r = body())) return r;
@@ -1971,8 +2009,10 @@ static gdf_status fuse_stack_plain(const uint8_t *stack_all, int S_all, int H, i
         for (const void *p : {(const void *)stack_all, (const void *)f, (const void *)g_smooth, (const void *)ws,
                               (const void *)s})
             key_push(key, p);
+        key_push(key, report != nullptr);
         if ((r = run_captured(key, R, o, body))) return r;
         if (!report) return GDF_OK;   // asynchronous: nothing waits for the device
+        if ((r = solve_body(R, x, BODY_REST))) return r;
     }
     std::vector<SliceState> h;
     const gdf_status st = collect(P, ws, s, report, tol, mixed ? o.inner : 1, &h);
@@ -2275,7 +2315,8 @@ static gdf_status solve_slices_plain(int n, const gdf_slice_desc *d, int gs_dtyp
     R.tol = tol;
     R.max_cycles = o.max_vc;
     R.stall_ratio = o.prec == GDF_PREC_FP32 ? kStallRatio : 0.0;
-    SolveIO x{gs_dtype, go_dtype, gs, go, f, fin_rows_ok(io)};
+    const bool rows = !P.periodic && march_rows(P);
+    SolveIO x{gs_dtype, go_dtype, gs, go, f, rows ? R.r_ftiles : R.r_tiles, R.partd2};
 
     auto body = [&]() -> gdf_status {
         {
@@ -2284,11 +2325,11 @@ static gdf_status solve_slices_plain(int n, const gdf_slice_desc *d, int gs_dtyp
                 HIP_TRY(launch_pprep(P.fp64, gs_dtype, gs, go_dtype, go, R.io, R.plaunch(), R.partd, R.partd2,
                                      R.partd3, s));
             else
-                HIP_TRY(launch_prep(P.fp64, gs_dtype, gs, go_dtype, go, R.io, n, P.n_tiles, R.desc, R.partd,
+                HIP_TRY(launch_prep(P.fp64, rows, gs_dtype, gs, go_dtype, go, R.io, n, rows ? P.n_ftiles : P.n_tiles, R.desc, R.partd,
                                     R.partd2, R.partd3, s));
         }
-        HIP_TRY(launch_finish_rhs(n, P.max_tiles, R.r_tiles, R.partd, R.partd2, R.partd3, R.st, s));
-        return solve_body(R, x);
+        HIP_TRY(launch_finish_rhs(n, R.max_slots(x.range_b), x.range_b, R.partd, R.partd2, R.partd3, R.st, s));
+        return solve_body(R, x, o.use_graph && report ? BODY_SHORT : BODY_ALL);
     };
 
     if (!o.use_graph) {
@@ -2296,6 +2337,7 @@ static gdf_status solve_slices_plain(int n, const gdf_slice_desc *d, int gs_dtyp
     } else {
         std::vector<unsigned long long> key;
         key_push(key, n);
+        key_push(key, bc);
         key_push(key, (const void *)ws);
         key_push(key, gs);
         key_push(key, go);
@@ -2326,8 +2368,10 @@ static gdf_status solve_slices_plain(int n, const gdf_slice_desc *d, int gs_dtyp
             key_push(key, d[i].pitch_go);
             key_push(key, d[i].pitch_f);
         }
+        key_push(key, report != nullptr);
         if ((r = run_captured(key, R, o, body))) return r;
         if (!report) return GDF_OK;   // asynchronous: nothing waits for the device
+        if ((r = solve_body(R, x, BODY_REST))) return r;
     }
     std::vector<SliceState> h;
     const gdf_status st = collect(P, ws, s, report, tol, o.prec == GDF_PREC_MIXED ? o.inner : 1, &h);
@@ -2412,29 +2456,30 @@ static gdf_status backward_plain(int n, const gdf_slice_desc *d, int dtype, cons
     }
     HIP_TRY(launch_finish_rhs(n, P.max_tiles, R.r_tiles, R.partd, R.partd, R.partd3, R.st, s));
     if (P.mixed) {
-        if ((r = mixed_iterate(R, dtype, nullptr, GDF_F32, nullptr, grad_f))) return r;
+        if ((r = mixed_iterate(R, dtype, nullptr, GDF_F32, nullptr, grad_f, R.r_tiles, R.partd))) return r;
     } else {
         if ((r = R.iterate(P.fp64))) return r;
     }
+    const bool need_da = grad_alpha || grad_alpha_sum;
+    double *const part_da = need_da ? R.partd : nullptr;
     {
         ProfScope ps(PC_ADJOINT, 0.0, s, false);
         if (P.periodic) {
             const PLaunch a = R.plaunch();
             HIP_TRY(launch_padjoint(P.fp64, gs, f, grad_gs, grad_go, R.io, n, a, R.st, P.mixed ? R.u64tab : nullptr,
-                                    R.partd, s));
+                                    part_da, s));
         } else {
             HIP_TRY(launch_adjoint_assemble(P.fp64, gs, f, grad_gs, grad_go, R.io, n, P.n_tiles, R.desc, R.st,
-                                            P.mixed ? R.u64tab : nullptr, R.partd, s));
+                                            P.mixed ? R.u64tab : nullptr, part_da, s));
         }
     }
-    if ((r = R.finish(R.r_tiles, nullptr, R.partd, FIN_SUM, 0))) return r;
+    if (need_da && (r = R.finish(R.r_tiles, nullptr, R.partd, FIN_SUM, 0))) return r;
     if (grad_alpha_sum) HIP_TRY(launch_sum_aux(n, R.st, grad_alpha_sum, s));
-    std::vector<SliceState> h(n);
-    HIP_TRY(hipMemcpyAsync(h.data(), R.st, sizeof(SliceState) * n, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    if (grad_alpha)
+    std::vector<SliceState> h;
+    const gdf_status st = collect(P, ws, s, report, tol, 1, &h);
+    if (grad_alpha && st != GDF_EDEVICE)
         for (int i = 0; i < n; ++i) grad_alpha[i] = h[i].aux;
-    return collect(P, ws, s, report, tol, 1);
+    return st;
 }
 
 // ------------------------------------------------------ solve_slices_noalloc

@@ -117,7 +117,7 @@ struct SliceState {
 enum FinishMode {
     FIN_BB = 0,       // store the sum as ||b||^2
     FIN_CHECK = 1,    // in-loop residual: store rr/rel, count the cycle, clear `active` when done
-    FIN_FINAL = 2,    // residual of the returned f: store rr/rel
+    FIN_FINAL = 2,    // residual of the returned f: store rr/rel (count_cycle: not of slices still active)
     FIN_INIT = 3,     // ||b_u||^2: rel_init = sqrt(sum / bb)
     FIN_SUM = 4,      // plain sum into state.aux (e.g. dLoss/dalpha)
     FIN_MEAN = 5      // sum of b: bmean = sum / npx, uoff = bmean / alpha
@@ -170,8 +170,9 @@ struct SliceIO {        // per-slice user-buffer view (element offsets/pitches)
 };
 
 // b_u = alpha (g_s - g_o) into level 0 b, and FP64 partials of
-// ||alpha g_s + L g_o||^2, ||b_u||^2 and sum(b_u) per tile.
-hipError_t launch_prep(bool fp64, int gs_dtype, const void *gs, int go_dtype, const void *go,
+// ||alpha g_s + L g_o||^2, ||b_u||^2 and sum(b_u) per tile (rows: per block, as
+// in launch_finalize).
+hipError_t launch_prep(bool fp64, bool rows, int gs_dtype, const void *gs, int go_dtype, const void *go,
                        const SliceIO *io_dev, int n_slices, long long n_tiles,
                        const LevelDesc *levs, double *part_bb, double *part_b0, double *part_bs,
                        hipStream_t s);
@@ -180,8 +181,7 @@ hipError_t launch_prep(bool fp64, int gs_dtype, const void *gs, int go_dtype, co
 // level-0 iterate of slice s is buffer (state[s].cycles & 1).
 // With `only` non-null, tiles of slices with only[s] == 0 are skipped.
 // rows: the row-marching kernel over blocks of kFinCols x kFinRows (n_tiles
-// of those; every width a multiple of 4 and the g_o and f rows aligned to four
-// elements), else the quad kernel over 64 x 16 tiles.
+// of those; every width at least 4), else the quad kernel over 64 x 16 tiles.
 constexpr int kFinCols = 256, kFinRows = 64;
 hipError_t launch_finalize(bool fp64, bool rows, int go_dtype, const void *go, int out_dtype, void *f,
                            const SliceIO *io_dev, int n_slices, long long n_tiles,
@@ -194,7 +194,8 @@ hipError_t launch_prep_adjoint(bool fp64, const void *grad_f, const SliceIO *io_
                                double *part_bs, hipStream_t s);
 
 // From lambda (level-0 iterate): grad_gs = alpha lambda, grad_go = L lambda,
-// partials of lambda . (g_s - f).  Buffers share the dtype of the solve.
+// partials of lambda . (g_s - f) (part_da null: not formed, g_s and f not read).
+// Buffers share the dtype of the solve.
 // With u64 non-null, lambda is the FP64 iterate of the mixed solve (buffer
 // state[s].cycles & 1) instead of the level-0 working-precision iterate.
 hipError_t launch_adjoint_assemble(bool fp64, const void *gs, const void *f, void *grad_gs,
@@ -204,7 +205,7 @@ hipError_t launch_adjoint_assemble(bool fp64, const void *gs, const void *f, voi
                                    hipStream_t s);
 
 // Mixed precision refinement step: u64_out = u64_in + e (e = level-0 FP32
-// iterate, buffer e_sel; skipped when first), r = alpha (g_s - g_o) - A u64_out
+// iterate, buffer e_sel; u64_in zero and not read when first), r = alpha (g_s - g_o) - A u64_out
 // in FP64, written as FP32 into level-0 b, partials of ||r||^2.
 struct RefineArgs {
     int gs_dtype, go_dtype;
@@ -217,7 +218,7 @@ struct RefineArgs {
     const LevelDesc *levs;   // FP32 hierarchy
     double *const *u64;      // [2][n_slices] device table of FP64 iterates (pitch = level-0 pitch)
     int in_sel, e_sel;       // which FP64 buffer is read; which FP32 level-0 buffer holds e
-    int first;               // 1: no correction to add (u64_in = 0)
+    int first;               // 1: u64_in = 0, not read
     const int *active;
     double *part_rr;
 };

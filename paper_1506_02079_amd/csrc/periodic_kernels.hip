@@ -141,7 +141,7 @@ __global__ __launch_bounds__(256) void pfinalize_kernel(const TO *go, TF *f, con
 }
 
 // Mixed refinement: u64_out = u64_in + e (e = level-0 FP32 iterate, buffer
-// r.e_sel; not on the first step), r = rhs - A u64_out in FP64 with
+// r.e_sel; u64_in is zero, and not read, on the first step), r = rhs - A u64_out in FP64 with
 // rhs = alpha (g_s - g_o) or r.rhs, stored as FP32 into level-0 b; ||r||^2.
 template <typename TS, typename TO>
 __global__ __launch_bounds__(256) void prefine_kernel(RefineArgs r, PLaunch a)
@@ -161,7 +161,7 @@ __global__ __launch_bounds__(256) void prefine_kernel(RefineArgs r, PLaunch a)
         const int x = it.x0 + (threadIdx.x & 63);
         auto unew = [&](int y, int xx) -> double {
             const long long q = (long long)y * pl + xx;
-            return r.first ? 0.0 : uin[q] + (double)e[q];
+            return (r.first ? 0.0 : uin[q]) + (double)e[q];
         };
         if (x < P.W) {
 #pragma unroll
@@ -207,8 +207,10 @@ __global__ __launch_bounds__(256) void padjoint_kernel(const T *gs, const T *f, 
     const PTile it = ptile(a, io);
     const SliceIO P = io[it.slice];
     const LevelDesc L = a.levs[P.lev0];
-    const TL *lam = u64 ? reinterpret_cast<const TL *>(u64[(st[it.slice].cycles & 1) * n + it.slice])
+    const int cycles = st[it.slice].cycles;
+    const TL *lam = u64 ? reinterpret_cast<const TL *>(u64[(cycles & 1) * n + it.slice])
                         : static_cast<const TL *>(L.u[a.in_sel]);
+    const bool zero = u64 && cycles == 0;   // no refinement step: still zero, and never written
     const double shift = u64 ? 0.0 : st[it.slice].shift + st[it.slice].uoff;   // constant parts of lambda
     const int x = it.x0 + (threadIdx.x & 63);
     double sda = 0.0;
@@ -217,13 +219,14 @@ __global__ __launch_bounds__(256) void padjoint_kernel(const T *gs, const T *f, 
         for (int i = 0; i < kPRows; ++i) {
             const int y = it.y0 + (threadIdx.x >> 6) + 4 * i;
             if (y >= P.H) break;
-            const double l = ldd(lam, (long long)y * L.pitch + x) + shift;
+            const double l = zero ? 0.0 : ldd(lam, (long long)y * L.pitch + x) + shift;
             const long long fo = P.off_f + (long long)y * P.pitch_f + x;
             if (ggs) ggs[fo] = (T)(P.alpha * l);
-            if (ggo) ggo[fo] = (T)plap(lam, 0, L.pitch, P.H, P.W, y, x);   // L is blind to the shift
-            sda += l * (ldd(gs, P.off_gs + (long long)y * P.pitch_gs + x) - ldd(f, fo));
+            if (ggo) ggo[fo] = zero ? T(0) : (T)plap(lam, 0, L.pitch, P.H, P.W, y, x);   // L is blind to the shift
+            if (part_da) sda += l * (ldd(gs, P.off_gs + (long long)y * P.pitch_gs + x) - ldd(f, fo));
         }
     }
+    if (!part_da) return;
     const double t = pblock_sum(sda, red);
     if (threadIdx.x == 0) part_da[blockIdx.x] = t;
 }

@@ -102,9 +102,12 @@ template <typename S> struct RBView {
 template <typename S> struct RowView {
     const S *u;
     long long pitch;
-    __device__ RowView(const S *u_, long long pitch_) : u(u_), pitch(pitch_) {}
-    __device__ double at(int x, int y) const { return (double)u[(long long)y * pitch + x]; }
-    __device__ void quad(int x, int y, int nvalid, double v[4]) const { load4(u, (long long)y * pitch + x, nvalid, v); }
+    __device__ RowView(const S *u_, long long pitch_) : u(u_), pitch(pitch_) {}   // u null: all zero
+    __device__ double at(int x, int y) const { return u ? (double)u[(long long)y * pitch + x] : 0.0; }
+    __device__ void quad(int x, int y, int nvalid, double v[4]) const
+    {
+        load4(u, (long long)y * pitch + x, u ? nvalid : 0, v);
+    }
 };
 
 template <typename TV>
@@ -241,6 +244,7 @@ __global__ __launch_bounds__(NT) void finish_kernel(int n_slices, const int *ran
         S.uoff = S.bmean / S.alpha;
         break;
     case FIN_FINAL:
+        if (count_cycle && active[sidx]) return;   // still iterating: its state stays the in-loop one
         S.rr = sum;
         S.rel = S.bb > 0.0 ? sqrt(sum / S.bb) : sqrt(sum);
         if (!isfinite(sum)) S.status = 6;  // GDF_ENONFINITE
@@ -370,6 +374,95 @@ hipError_t launch_resume_flags(int n_slices, const SliceState *state, double tol
     return hipGetLastError();
 }
 
+// -------------------------------------------------------- row marching ---
+
+constexpr int kFinQ = 4;   // rows of loads in flight
+
+__device__ __forceinline__ int find_fslice(const SliceIO *io, int n, long long t)
+{
+    int lo = 0, hi = n - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (io[mid].ftile_begin <= t) lo = mid; else hi = mid - 1;
+    }
+    return lo;
+}
+
+// lane i receives lane i - 1's / i + 1's value (0 at the wave's ends)
+__device__ __forceinline__ double wave_prev(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), 0x138, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x138, 0xF, 0xF, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+__device__ __forceinline__ double wave_next(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), 0x130, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x130, 0xF, 0xF, true);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+template <typename V> __device__ __forceinline__ void v4_to_d(const V &q, double v[4])
+{
+    v[0] = (double)q.x;
+    v[1] = (double)q.y;
+    v[2] = (double)q.z;
+    v[3] = (double)q.w;
+}
+
+#define GDF_GLOBAL __attribute__((address_space(1)))
+
+// four elements starting on any element
+template <typename T> struct Vec4U { typedef T type __attribute__((ext_vector_type(4), aligned(sizeof(T)))); };
+
+// q[d], q[d + 1], ... at the front (d in 0 .. 3; what is behind them repeats q[3])
+template <typename V> __device__ __forceinline__ V shift_down(const V &q, int d)
+{
+    V r;
+    r.x = d == 0 ? q.x : d == 1 ? q.y : d == 2 ? q.z : q.w;
+    r.y = d == 0 ? q.y : d == 1 ? q.z : q.w;
+    r.z = d == 0 ? q.z : q.w;
+    r.w = q.w;
+    return r;
+}
+
+// A row block of the marching passes: this wave's columns and rows.
+struct RowBlock {
+    int si, H, W, X0, Y0, Y1;
+    int x, nv;      // the lane's first pixel and the pixels of its quad inside the row (<= 0: none)
+    int xa, xo, d;  // quad in padded arena rows; quad in caller rows, and its shift
+    bool in, tail;  // the lane has pixels; (uniform) the row ends inside some lane's quad
+};
+__device__ __forceinline__ RowBlock row_block(const SliceIO *io, int si, long long ft)
+{
+    RowBlock b;
+    b.si = si;
+    b.H = __builtin_amdgcn_readfirstlane(io[si].H);
+    b.W = __builtin_amdgcn_readfirstlane(io[si].W);
+    const int ftx = __builtin_amdgcn_readfirstlane(io[si].ftiles_x);
+    const int lt = __builtin_amdgcn_readfirstlane((int)(ft - io[si].ftile_begin));
+    b.X0 = lt % ftx * kFinCols;
+    b.Y0 = lt / ftx * kFinRows;
+    b.Y1 = min(b.Y0 + kFinRows, b.H);
+    b.x = b.X0 + 4 * (int)threadIdx.x;
+    b.nv = min(4, b.W - b.x);
+    b.in = b.nv > 0;
+    b.tail = (b.W & 3) && b.W - b.X0 <= kFinCols;
+    b.xa = min(b.x, (b.W - 1) & ~3);
+    b.xo = min(b.x, b.W - 4);
+    b.d = min(b.x - b.xo, 3);
+    return b;
+}
+// a partial quad's missing pixels repeat its last one
+__device__ __forceinline__ void fill_quad(int nv, double v[4])
+{
+    v[1] = nv > 1 ? v[1] : v[0];
+    v[2] = nv > 2 ? v[2] : v[1];
+    v[3] = nv > 3 ? v[3] : v[2];
+}
+
 // --------------------------------------------------------------- prep ---
 
 // b_u = alpha (g_s - g_o) and partial sums of ||alpha g_s + L g_o||^2, ||b_u||^2
@@ -426,32 +519,155 @@ __global__ __launch_bounds__(256) void prep_kernel(const TS *gs, const TO *go, c
     }
 }
 
-template <typename T, typename TS>
-static hipError_t prep_go(int go_dtype, const void *gs, const void *go, const SliceIO *io, int n,
-                          long long nt, const LevelDesc *levs, double *pbb, double *pb0,
-                          double *pbs, hipStream_t s)
+// The same by row marching (see finalize_kernel): one wave per kFinCols x kFinRows
+// block holds g_o's rows y - 1, y, y + 1, so each is read once, and the slice
+// lookup and the block's sums are paid once per 16384 pixels instead of per 1024.
+// 96 slices of 512 to 4096 a side (510 Mpx, 9 B per pixel): 1.90 ms as quads, 0.85 ms
+// (5.4 TB/s) marched.
+template <typename T, typename TS, typename TO>
+__global__ __launch_bounds__(64) void prep_rows_kernel(const TS *gs_, const TO *go_, const SliceIO *io, int n_slices,
+                                                       long long n_ft, const LevelDesc *levs, double *part_bb,
+                                                       double *part_b0, double *part_bs)
 {
-    const dim3 g((unsigned)nt), blk(256);
-    if (go_dtype == 0)
-        hipLaunchKernelGGL((prep_kernel<T, TS, uint8_t>), g, blk, 0, s, (const TS *)gs, (const uint8_t *)go, io, n, nt, levs, pbb, pb0, pbs);
-    else if (go_dtype == 1)
-        hipLaunchKernelGGL((prep_kernel<T, TS, float>), g, blk, 0, s, (const TS *)gs, (const float *)go, io, n, nt, levs, pbb, pb0, pbs);
-    else
-        hipLaunchKernelGGL((prep_kernel<T, TS, double>), g, blk, 0, s, (const TS *)gs, (const double *)go, io, n, nt, levs, pbb, pb0, pbs);
-    return hipGetLastError();
+    using VT = typename Vec4<T>::type;
+    using VS = typename Vec4U<TS>::type;
+    using VO = typename Vec4U<TO>::type;
+    constexpr int Q = kFinQ;
+    const long long ft = xcd_tile(blockIdx.x, gridDim.x);
+    if (ft >= n_ft) return;
+    const int si = find_fslice(io, n_slices, ft);
+    const RowBlock B = row_block(io, si, ft);
+    const int H = B.H, W = B.W, X0 = B.X0, Y0 = B.Y0, Y1 = B.Y1, xa = B.xa, xo = B.xo;
+    const bool tail = B.tail;
+    const double al = io[si].alpha;
+    const long long pb = levs[io[si].lev0].pitch;
+    GDF_GLOBAL T *b = (GDF_GLOBAL T *)levs[io[si].lev0].b;
+    const long long pitch_gs = io[si].pitch_gs, pitch_go = io[si].pitch_go;
+    const GDF_GLOBAL TS *gs = (const GDF_GLOBAL TS *)gs_ + io[si].off_gs;
+    const GDF_GLOBAL TO *go = (const GDF_GLOBAL TO *)go_ + io[si].off_go;
+    const int lane = threadIdx.x;
+    // the wave's outer neighbour columns (lane 0: left, lane 63: right), clamped
+    const int xe = min(max(lane == 0 ? X0 - 1 : X0 + kFinCols, 0), W - 1);
+    const double ml = B.x > 0 ? 1.0 : 0.0, mr = B.x + 3 < W - 1 ? 1.0 : 0.0;
+    auto oquad = [&](int y) -> VO {
+        return *reinterpret_cast<const GDF_GLOBAL VO *>(go + (long long)min(max(y, 0), H - 1) * pitch_go + xo);
+    };
+    auto quad_d = [&](const VO &q, double v[4]) {
+        v4_to_d(tail ? shift_down(q, B.d) : q, v);
+        if (tail) fill_quad(B.nv, v);
+    };
+    double on[4], oc[4], os[4];
+    quad_d(oquad(Y0 - 1), on);   // (row -1: masked below)
+    quad_d(oquad(Y0), oc);
+    double oe = (double)go[(long long)Y0 * pitch_go + xe];
+    // queue: g_o of row y + 1 (and its outer element), g_s of row y; past the
+    // block's last row it re-reads that row
+    VO qo[Q];
+    VS qs[Q];
+    TO qe[Q];
+    auto issue = [&](int t, int slot) {
+        const int y = min(Y0 + t, Y1 - 1), yn = min(y + 1, H - 1);
+        qo[slot] = oquad(yn);
+        qe[slot] = go[(long long)yn * pitch_go + xe];
+        qs[slot] = *reinterpret_cast<const GDF_GLOBAL VS *>(gs + (long long)y * pitch_gs + xo);
+    };
+#pragma unroll
+    for (int q = 0; q < Q - 1; ++q) issue(q, q);
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0) (see finalize_kernel)
+    double sbb = 0.0, sb0 = 0.0, sbs = 0.0;
+    const int n_rows = Y1 - Y0;
+    for (int tb = 0; tb < n_rows; tb += Q) {
+#pragma unroll
+        for (int k = 0; k < Q; ++k) {
+            const int t = tb + k;
+            issue(t + Q - 1, (k + Q - 1) % Q);
+            const int y = Y0 + t;
+            const double mu = y > 0 ? 1.0 : 0.0, md = y < H - 1 ? 1.0 : 0.0;   // uniform
+            const bool keep = t < n_rows && B.in;
+            double sv[4];
+            quad_d(qo[k], os);
+            v4_to_d(tail ? shift_down(qs[k], B.d) : qs[k], sv);
+            const double oe_next = (double)qe[k];
+            double ol = wave_prev(oc[3]), orr = wave_next(oc[0]);
+            ol = lane == 0 ? oe : ol;
+            orr = lane == 63 ? oe : orr;
+            VT bv;
+            double rbb = 0.0, rb0 = 0.0, rbs = 0.0;
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                const double l = m == 0 ? ol : oc[m - 1], r = m == 3 ? orr : oc[m + 1];
+                double lap = (m == 0 ? ml : 1.0) * (oc[m] - l);   // (L g_o)_p over in-slice neighbours
+                lap = fma(m == 3 ? mr : 1.0, oc[m] - r, lap);
+                lap = fma(mu, oc[m] - on[m], lap);
+                lap = fma(md, oc[m] - os[m], lap);
+                const double bf = al * sv[m] + lap;
+                const T bu = (T)(al * (sv[m] - oc[m]));
+                bv[m] = bu;
+                const bool w = !tail || m < B.nv;
+                const double bd = w ? (double)bu : 0.0, bfw = w ? bf : 0.0;
+                rbb = fma(bfw, bfw, rbb);
+                rb0 = fma(bd, bd, rb0);
+                rbs += bd;
+            }
+            sbb += keep ? rbb : 0.0;
+            sb0 += keep ? rb0 : 0.0;
+            sbs += keep ? rbs : 0.0;
+            // (arena rows are padded: a whole quad may be stored past the row's end)
+            if (keep) *reinterpret_cast<GDF_GLOBAL VT *>(b + (long long)y * pb + xa) = bv;
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                on[m] = oc[m];
+                oc[m] = os[m];
+            }
+            oe = oe_next;
+        }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        sbb += __shfl_xor(sbb, off);
+        sb0 += __shfl_xor(sb0, off);
+        sbs += __shfl_xor(sbs, off);
+    }
+    if (lane == 0) {
+        part_bb[ft] = sbb;
+        part_b0[ft] = sb0;
+        part_bs[ft] = sbs;
+    }
 }
 
-hipError_t launch_prep(bool fp64, int gs_dtype, const void *gs, int go_dtype, const void *go,
+template <typename T, typename TS, typename TO>
+static hipError_t prep_launch(bool rows, const void *gs, const void *go, const SliceIO *io, int n, long long nt,
+                              const LevelDesc *levs, double *pbb, double *pb0, double *pbs, hipStream_t s)
+{
+    const dim3 g((unsigned)nt);
+    if (rows)
+        hipLaunchKernelGGL((prep_rows_kernel<T, TS, TO>), g, dim3(64), 0, s, (const TS *)gs, (const TO *)go, io, n, nt,
+                           levs, pbb, pb0, pbs);
+    else
+        hipLaunchKernelGGL((prep_kernel<T, TS, TO>), g, dim3(256), 0, s, (const TS *)gs, (const TO *)go, io, n, nt, levs,
+                           pbb, pb0, pbs);
+    return hipGetLastError();
+}
+template <typename T, typename TS>
+static hipError_t prep_go(bool rows, int go_dtype, const void *gs, const void *go, const SliceIO *io, int n,
+                          long long nt, const LevelDesc *levs, double *pbb, double *pb0, double *pbs, hipStream_t s)
+{
+    if (go_dtype == 0) return prep_launch<T, TS, uint8_t>(rows, gs, go, io, n, nt, levs, pbb, pb0, pbs, s);
+    if (go_dtype == 1) return prep_launch<T, TS, float>(rows, gs, go, io, n, nt, levs, pbb, pb0, pbs, s);
+    return prep_launch<T, TS, double>(rows, gs, go, io, n, nt, levs, pbb, pb0, pbs, s);
+}
+
+hipError_t launch_prep(bool fp64, bool rows, int gs_dtype, const void *gs, int go_dtype, const void *go,
                        const SliceIO *io_dev, int n_slices, long long n_tiles,
                        const LevelDesc *levs, double *part_bb, double *part_b0, double *part_bs,
                        hipStream_t s)
 {
     if (n_tiles <= 0) return hipSuccess;
     if (fp64)
-        return gs_dtype == 2 ? prep_go<double, double>(go_dtype, gs, go, io_dev, n_slices, n_tiles, levs, part_bb, part_b0, part_bs, s)
-                             : prep_go<double, float>(go_dtype, gs, go, io_dev, n_slices, n_tiles, levs, part_bb, part_b0, part_bs, s);
-    return gs_dtype == 2 ? prep_go<float, double>(go_dtype, gs, go, io_dev, n_slices, n_tiles, levs, part_bb, part_b0, part_bs, s)
-                         : prep_go<float, float>(go_dtype, gs, go, io_dev, n_slices, n_tiles, levs, part_bb, part_b0, part_bs, s);
+        return gs_dtype == 2 ? prep_go<double, double>(rows, go_dtype, gs, go, io_dev, n_slices, n_tiles, levs, part_bb, part_b0, part_bs, s)
+                             : prep_go<double, float>(rows, go_dtype, gs, go, io_dev, n_slices, n_tiles, levs, part_bb, part_b0, part_bs, s);
+    return gs_dtype == 2 ? prep_go<float, double>(rows, go_dtype, gs, go, io_dev, n_slices, n_tiles, levs, part_bb, part_b0, part_bs, s)
+                         : prep_go<float, float>(rows, go_dtype, gs, go, io_dev, n_slices, n_tiles, levs, part_bb, part_b0, part_bs, s);
 }
 
 // ----------------------------------------------------------- finalize ---
@@ -511,67 +727,34 @@ __global__ __launch_bounds__(256) void finalize_quad_kernel(const TO *go, TF *f,
     if (threadIdx.x == 0) part_rr[c.tile] = t;
 }
 
-// Row-marching output pass (the common case: widths are multiples of four
-// and the g_o and f rows start on four-element boundaries).  One wave owns a block of kFinCols columns (four
+// Row-marching passes (every width at least 4).  g_o, g_s and f rows may start
+// on any element: their quads are moved with accesses that need no more than
+// element alignment (one instruction either way), and where a row ends inside a
+// lane's quad (nv < 4 pixels) the lane loads the row's last four pixels and
+// shifts them down.  33 x 1021 x 1531 (nothing aligned): the quad pass took 254 us, this 148.
+//
+// The output pass.  One wave owns a block of kFinCols columns (four
 // per lane) by kFinRows rows and walks down it holding the iterate's rows
 // y - 1, y, y + 1, so every row is read once; the loads of the next rows are
 // in flight kFinQ - 1 rows ahead.  The wave's two outer horizontal neighbours
 // come from one extra element per row; the others cross lanes by DPP.
-constexpr int kFinQ = 4;   // rows of loads in flight
-
-__device__ __forceinline__ int find_fslice(const SliceIO *io, int n, long long t)
-{
-    int lo = 0, hi = n - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (io[mid].ftile_begin <= t) lo = mid; else hi = mid - 1;
-    }
-    return lo;
-}
-
-// lane i receives lane i - 1's / i + 1's value (0 at the wave's ends)
-__device__ __forceinline__ double wave_prev(double v)
-{
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), 0x138, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x138, 0xF, 0xF, true);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-__device__ __forceinline__ double wave_next(double v)
-{
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(b & 0xffffffffll), 0x130, 0xF, 0xF, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x130, 0xF, 0xF, true);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
-
-template <typename V> __device__ __forceinline__ void v4_to_d(const V &q, double v[4])
-{
-    v[0] = (double)q.x;
-    v[1] = (double)q.y;
-    v[2] = (double)q.z;
-    v[3] = (double)q.w;
-}
-
-#define GDF_GLOBAL __attribute__((address_space(1)))
-
 template <typename T, typename TO, typename TF>
 __global__ __launch_bounds__(64) void finalize_kernel(const TO *go_, TF *f_, const SliceIO *io, int n_slices,
                                                       long long n_ft, const LevelDesc *levs,
                                                       const SliceState *st, const int *only, double *part_rr)
 {
     using VT = typename Vec4<T>::type;
-    using VO = typename Vec4<TO>::type;
-    using VF = typename Vec4<TF>::type;
+    using VO = typename Vec4U<TO>::type;
+    using VF = typename Vec4U<TF>::type;
     constexpr int Q = kFinQ;
     const long long ft = xcd_tile(blockIdx.x, gridDim.x);
     if (ft >= n_ft) return;
     const int si = find_fslice(io, n_slices, ft);
     if (only && !only[si]) return;   // uniform per wave: keeps this slice's partial sum
     // the slice's fields as wave-uniform scalars (stores to f cannot alias them)
-    const int H = __builtin_amdgcn_readfirstlane(io[si].H), W = __builtin_amdgcn_readfirstlane(io[si].W);
-    const int ftx = __builtin_amdgcn_readfirstlane(io[si].ftiles_x);
-    const long long lt = ft - io[si].ftile_begin;
+    const RowBlock B = row_block(io, si, ft);
+    const int H = B.H, W = B.W, X0 = B.X0, Y0 = B.Y0, Y1 = B.Y1, x = B.x, xa = B.xa, xo = B.xo;
+    const bool in = B.in, tail = B.tail;
     const long long off_go = io[si].off_go, pitch_go = io[si].pitch_go;
     const long long off_f = io[si].off_f, pitch_f = io[si].pitch_f;
     const double sg = io[si].alpha;
@@ -586,19 +769,14 @@ __global__ __launch_bounds__(64) void finalize_kernel(const TO *go_, TF *f_, con
     const double shift = st[si].shift + st[si].uoff;
 
     const int lane = threadIdx.x;
-    const int X0 = (int)(lt % ftx) * kFinCols, Y0 = (int)(lt / ftx) * kFinRows;
-    const int Y1 = min(Y0 + kFinRows, H);
-    const int x = X0 + 4 * lane;
-    const bool in = x < W;          // the lane's quad lies in the slice (W is a multiple of 4)
-    const int xl = min(x, W - 4);   // a valid quad for every lane
     // the wave's outer neighbour columns (lane 0: left, lane 63: right), clamped
     const int xe = min(max(lane == 0 ? X0 - 1 : X0 + kFinCols, 0), W - 1);
     // horizontal neighbour masks of the quad's first and last pixel
     const double ml = x > 0 ? 1.0 : 0.0, mr = x + 3 < W - 1 ? 1.0 : 0.0;
     // The iterate stores each row by colour (LevelDesc): pixel (x, y) at
     // element x / 2 of the half (x + y) & 1 of row y (halves pu / 2 long).  A
-    // lane's quad (xl a multiple of 4) is two pairs: pixels xl, xl + 2 of one
-    // colour and xl + 1, xl + 3 of the other.  Rows are clamped into the slice;
+    // lane's quad (xa a multiple of 4) is two pairs: pixels xa, xa + 2 of one
+    // colour and xa + 1, xa + 3 of the other.  Rows are clamped into the slice;
     // arena rows are multiples of 64 elements, so a pair never leaves its half.
     using VT2 = typename Vec2<T>::type;
     const long long pu2 = pu >> 1;
@@ -606,17 +784,19 @@ __global__ __launch_bounds__(64) void finalize_kernel(const TO *go_, TF *f_, con
         const int yc = min(max(y, 0), H - 1);
         return u[(long long)yc * pu + ((x + yc) & 1) * pu2 + (x >> 1)];
     };
-    auto uquad = [&](int y, VT2 &ev, VT2 &od) {   // the colours of pixels xl (ev) and xl + 1 (od)
+    auto uquad = [&](int y, VT2 &ev, VT2 &od) {   // the colours of pixels xa (ev) and xa + 1 (od)
         const int yc = min(max(y, 0), H - 1);
-        const GDF_GLOBAL T *r0 = u + (long long)yc * pu + (xl >> 1);
+        const GDF_GLOBAL T *r0 = u + (long long)yc * pu + (xa >> 1);
         ev = *reinterpret_cast<const GDF_GLOBAL VT2 *>((yc & 1) ? r0 + pu2 : r0);
         od = *reinterpret_cast<const GDF_GLOBAL VT2 *>((yc & 1) ? r0 : r0 + pu2);
     };
-    auto quad_d = [](const VT2 &ev, const VT2 &od, double v[4]) {
+    auto quad_d = [&](const VT2 &ev, const VT2 &od, double v[4]) {
         v[0] = (double)ev.x;
         v[1] = (double)od.x;
         v[2] = (double)ev.y;
         v[3] = (double)od.y;
+        // (past the row's end: the last pixel again, so its difference is zero)
+        if (tail) fill_quad(B.nv, v);
     };
 
     double un[4], uc[4], us[4];
@@ -639,8 +819,8 @@ __global__ __launch_bounds__(64) void finalize_kernel(const TO *go_, TF *f_, con
         const int y = min(Y0 + t, Y1 - 1);
         uquad(y + 1, qev[slot], qod[slot]);
         qe[slot] = uat(xe, y + 1);
-        qb[slot] = *reinterpret_cast<const GDF_GLOBAL VT *>(bu + (long long)y * pu + xl);
-        qo[slot] = *reinterpret_cast<const GDF_GLOBAL VO *>(go + off_go + (long long)y * pitch_go + xl);
+        qb[slot] = *reinterpret_cast<const GDF_GLOBAL VT *>(bu + (long long)y * pu + xa);
+        qo[slot] = *reinterpret_cast<const GDF_GLOBAL VO *>(go + off_go + (long long)y * pitch_go + xo);
     };
 #pragma unroll
     for (int q = 0; q < Q - 1; ++q) issue(q, q);
@@ -661,7 +841,7 @@ __global__ __launch_bounds__(64) void finalize_kernel(const TO *go_, TF *f_, con
             double bb[4], o[4];
             quad_d(qev[k], qod[k], us);
             v4_to_d(qb[k], bb);
-            v4_to_d(qo[k], o);
+            v4_to_d(tail ? shift_down(qo[k], B.d) : qo[k], o);
             const double ue_next = (double)qe[k];
             double ul = wave_prev(uc[3]), ur = wave_next(uc[0]);
             ul = lane == 0 ? ue : ul;
@@ -677,12 +857,20 @@ __global__ __launch_bounds__(64) void finalize_kernel(const TO *go_, TF *f_, con
                 acc = fma(mu, uc[m] - un[m], acc);
                 acc = fma(md, uc[m] - us[m], acc);
                 const double res = bb[m] - sg * (uc[m] + shift) - acc;
-                rr = fma(res, res, rr);
+                rr = fma(tail && m >= B.nv ? 0.0 : res, res, rr);
                 fv[m] = (TF)(o[m] + (uc[m] + shift));
             }
             srr = fma(wrow, rr, srr);
-            if (t < n_rows && in)
-                *reinterpret_cast<GDF_GLOBAL VF *>(f + off_f + (long long)y * pitch_f + x) = fv;
+            if (t < n_rows && in) {
+                GDF_GLOBAL TF *fp = f + off_f + (long long)y * pitch_f + x;
+                if (!tail || B.nv == 4) {
+                    *reinterpret_cast<GDF_GLOBAL VF *>(fp) = fv;
+                } else {
+                    fp[0] = fv.x;
+                    if (B.nv > 1) fp[1] = fv.y;
+                    if (B.nv > 2) fp[2] = fv.z;
+                }
+            }
 #pragma unroll
             for (int m = 0; m < 4; ++m) {
                 un[m] = uc[m];
@@ -807,7 +995,7 @@ __device__ __forceinline__ void quad_lap(const View &v, const QuadCtx &q, int nv
 // grad_go = L lambda, partials of lambda . (g_s - f).
 template <typename T, typename View>
 __device__ __forceinline__ void adjoint_quad(const View &lam, double shift, const T *gs, const T *f, T *ggs,
-                                             T *ggo, const QuadCtx &q, double &sda)
+                                             T *ggo, const QuadCtx &q, bool need_da, double &sda)
 {
     const SliceIO &P = q.P;
     const int nv = q.row_in ? q.nvalid : 0;
@@ -815,8 +1003,8 @@ __device__ __forceinline__ void adjoint_quad(const View &lam, double shift, cons
     double lc[4], lap[4], g[4], fv[4], og[4], oo[4];
     quad_lap(lam, q, nv, lc, lap);   // L is blind to the constant shift
     const long long fo = P.off_f + (long long)y * P.pitch_f + q.x;
-    load4(gs, P.off_gs + (long long)y * P.pitch_gs + q.x, nv, g);
-    load4(f, fo, nv, fv);
+    load4(gs, P.off_gs + (long long)y * P.pitch_gs + q.x, need_da ? nv : 0, g);   // (zeros unless read)
+    load4(f, fo, need_da ? nv : 0, fv);
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
         const double l = lc[k] + shift;
@@ -839,15 +1027,18 @@ __global__ __launch_bounds__(256) void adjoint_kernel(const T *gs, const T *f, T
     if (!quad_ctx(io, n, n_tiles, c)) return;
     const SliceIO &P = c.P;
     const LevelDesc &L = levs[P.lev0];
-    const int par = st[c.si].cycles & 1;
+    const int cycles = st[c.si].cycles, par = cycles & 1;
+    const bool need_da = part_da != nullptr;
     double sda = 0.0;
-    if (u64) {
-        adjoint_quad<T>(RowView<double>(u64[par * n + c.si], L.pitch), 0.0, gs, f, ggs, ggo, c, sda);
+    if (u64) {   // (no refinement step: still zero, and never written)
+        adjoint_quad<T>(RowView<double>(cycles ? u64[par * n + c.si] : nullptr, L.pitch), 0.0, gs, f, ggs, ggo, c,
+                        need_da, sda);
     } else {
         const RBView<T> lam(static_cast<const T *>(L.u[par]), L.pitch);
         const double shift = st[c.si].shift + st[c.si].uoff;   // constant parts of lambda
-        adjoint_quad<T>(lam, shift, gs, f, ggs, ggo, c, sda);
+        adjoint_quad<T>(lam, shift, gs, f, ggs, ggo, c, need_da, sda);
     }
+    if (!need_da) return;
     const double t = block_sum(sda, red);
     if (threadIdx.x == 0) part_da[c.tile] = t;
 }
@@ -867,8 +1058,8 @@ hipError_t launch_adjoint_assemble(bool fp64, const void *gs, const void *f, voi
 
 // ---------------------------------------------------- mixed refinement ---
 
-// u64_out = u64_in + e (e: the FP32 correction of the last inner solve; the
-// first step starts from zero), then the FP64 residual of u64_out stored as
+// u64_out = u64_in + e (e: the FP32 correction of the last inner solve; u64_in is
+// zero in the first step, and not read), then the FP64 residual of u64_out stored as
 // the FP32 right-hand side of the next inner solve, and its squared norm.
 template <typename TS, typename TO>
 __global__ __launch_bounds__(256) void refine_kernel(RefineArgs a)
@@ -890,29 +1081,25 @@ __global__ __launch_bounds__(256) void refine_kernel(RefineArgs a)
         // new iterate on the quad and its four neighbour rows / columns
         double uc[4], un[4], us[4], t0[4], t1[4];
         double ul = 0.0, ur = 0.0;
-        if (a.first) {
+        const RowView<double> u0(a.first ? nullptr : uin, pl);
+        u0.quad(x, y, nv, uc);
+        e.quad(x, y, nv, t0);
+        u0.quad(x, y - 1, y > 0 ? nv : 0, un);
+        e.quad(x, y - 1, y > 0 ? nv : 0, t1);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) uc[k] = un[k] = us[k] = 0.0;
-        } else {
-            load4(uin, p, nv, uc);
-            e.quad(x, y, nv, t0);
-            load4(uin, p - pl, y > 0 ? nv : 0, un);
-            e.quad(x, y - 1, y > 0 ? nv : 0, t1);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                uc[k] += t0[k];
-                un[k] += t1[k];
-            }
-            load4(uin, p + pl, y < H - 1 ? nv : 0, us);
-            e.quad(x, y + 1, y < H - 1 ? nv : 0, t1);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) us[k] += t1[k];
+        for (int k = 0; k < 4; ++k) {
+            uc[k] += t0[k];
+            un[k] += t1[k];
         }
+        u0.quad(x, y + 1, y < H - 1 ? nv : 0, us);
+        e.quad(x, y + 1, y < H - 1 ? nv : 0, t1);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) us[k] += t1[k];
         ul = row_prev(uc[3]);
         ur = row_next(uc[0]);
         const int g = threadIdx.x & 15;
-        if (!a.first && nv > 0 && g == 0 && x > 0) ul = uin[p - 1] + e.at(x - 1, y);
-        if (!a.first && nv > 0 && g == 15 && x + nv < W) ur = uin[p + nv] + e.at(x + nv, y);
+        if (nv > 0 && g == 0 && x > 0) ul = u0.at(x - 1, y) + e.at(x - 1, y);
+        if (nv > 0 && g == 15 && x + nv < W) ur = u0.at(x + nv, y) + e.at(x + nv, y);
         double bv[4];
         if (a.rhs) {
             load4(static_cast<const TS *>(a.rhs), P.off_f + (long long)y * P.pitch_f + x, nv, bv);
@@ -973,12 +1160,13 @@ __global__ __launch_bounds__(256) void finalize64_kernel(const TO *go, TF *f, co
     QuadCtx c;
     if (!quad_ctx(io, n, n_tiles, c)) return;
     const SliceIO &P = c.P;
-    const double *u = u64[(st[c.si].cycles & 1) * n + c.si];   // latest FP64 iterate
-    const long long pl = levs[P.lev0].pitch;
+    // latest FP64 iterate (no refinement step: still zero, and never written)
+    const int cycles = st[c.si].cycles;
+    const RowView<double> u(cycles ? u64[(cycles & 1) * n + c.si] : nullptr, levs[P.lev0].pitch);
     const int y = min(c.y, P.H - 1), nv = c.row_in ? c.nvalid : 0;
     double o[4], uv[4];
     load4(go, P.off_go + (long long)y * P.pitch_go + c.x, nv, o);
-    load4(u, (long long)y * pl + c.x, nv, uv);
+    u.quad(c.x, y, nv, uv);
 #pragma unroll
     for (int k = 0; k < 4; ++k) o[k] += uv[k];
     store4(f, P.off_f + (long long)y * P.pitch_f + c.x, nv, o);
