@@ -288,14 +288,14 @@ hipError_t launch_block(BlockKind k, bool periodic, bool level0, int sweeps, boo
 // Slices with wrap-around (periodic) boundaries run the levels and finite-volume
 // operators of the Neumann hierarchy with the neighbours of the first and last
 // row and column taken across the wrap (the passes above).  Level-0 iterates
-// are row-major.  The per-pixel kernels (periodic_kernels.hip) run one workgroup
+// are row-major, in buffer 0 between cycles (a constant index: a runtime one into a
+// descriptor copy sends it to scratch memory).  The per-pixel kernels (periodic_kernels.hip) run one workgroup
 // per 64 x 16 pixel tile (SliceIO::tile_begin counts them slice by slice, so
 // per-slice partial sums occupy contiguous slots).
 struct PLaunch {
     const LevelDesc *levs;
     const int *slice_of;   // the slice of each tile
     int n_items;           // tiles
-    int in_sel;            // the level-0 buffer read
     double *part_rr;       // per-item sums of r^2
 };
 // Buffer element types (gdf_dtype values of the public header).
@@ -304,7 +304,7 @@ enum { GDF_DT_U8 = 0, GDF_DT_F32 = 1, GDF_DT_F64 = 2 };
 // ||b_u||^2, sum(b_u), with the periodic L; items of level 0
 hipError_t launch_pprep(bool fp64, int gs_dtype, const void *gs, int go_dtype, const void *go, const SliceIO *io,
                         const PLaunch &a, double *part_bb, double *part_b0, double *part_bs, hipStream_t s);
-// f = g_o + u (+ uoff + shift) from the level-0 buffer a.in_sel, FP64 partials
+// f = g_o + u (+ uoff + shift) from the level-0 buffer 0, FP64 partials
 // of the residual ||b_u - A u||^2; slices with only[s] == 0 skipped (only non-null)
 hipError_t launch_pfinalize(bool fp64, int go_dtype, const void *go, int out_dtype, void *f, const SliceIO *io,
                             const PLaunch &a, const SliceState *st, const int *only, hipStream_t s);

@@ -118,7 +118,7 @@ __global__ __launch_bounds__(256) void pfinalize_kernel(const TO *go, TF *f, con
     if (only && !only[it.slice]) return;   // uniform per block: keeps this slice's partial sum
     const SliceIO P = io[it.slice];
     const LevelDesc L = a.levs[P.lev0];
-    const T *u = static_cast<const T *>(L.u[a.in_sel]);
+    const T *u = static_cast<const T *>(L.u[0]);
     const T *b = static_cast<const T *>(L.b);
     const double shift = st[it.slice].shift + st[it.slice].uoff;
     const int x = it.x0 + (threadIdx.x & 63);
@@ -156,7 +156,7 @@ __global__ __launch_bounds__(256) void prefine_kernel(RefineArgs r, PLaunch a)
         const long long pl = L.pitch;
         const double *uin = r.u64[r.in_sel * r.n_slices + it.slice];
         double *uout = r.u64[(r.in_sel ^ 1) * r.n_slices + it.slice];
-        const float *e = static_cast<const float *>(L.u[r.e_sel]);
+        const float *e = static_cast<const float *>(L.u[0]);
         float *b = static_cast<float *>(L.b);
         const int x = it.x0 + (threadIdx.x & 63);
         auto unew = [&](int y, int xx) -> double {
@@ -209,7 +209,7 @@ __global__ __launch_bounds__(256) void padjoint_kernel(const T *gs, const T *f, 
     const LevelDesc L = a.levs[P.lev0];
     const int cycles = st[it.slice].cycles;
     const TL *lam = u64 ? reinterpret_cast<const TL *>(u64[(cycles & 1) * n + it.slice])
-                        : static_cast<const TL *>(L.u[a.in_sel]);
+                        : static_cast<const TL *>(L.u[0]);
     const bool zero = u64 && cycles == 0;   // no refinement step: still zero, and never written
     const double shift = u64 ? 0.0 : st[it.slice].shift + st[it.slice].uoff;   // constant parts of lambda
     const int x = it.x0 + (threadIdx.x & 63);
