@@ -36,8 +36,7 @@ namespace {
 
 #define GDF_G __attribute__((address_space(1)))
 
-constexpr int R = kBlockRows / kBlockWaves;   // rows per wave
-static_assert(R % 2 == 0, "a wave's first row is even: row parities are static");
+constexpr int kR = kBlockRows / kBlockWaves;   // rows per wave
 
 template <typename T> struct Quad { typedef T type __attribute__((ext_vector_type(4))); };
 
@@ -111,11 +110,13 @@ __device__ __forceinline__ void side_coef(int i, int n, T wl, T ke, T &w, T &kl,
 
 // PLAIN: both segments are plain (one stencil for every cell); otherwise
 // coefficients are per lane and per row.
-template <typename T, typename SO, typename SC, bool PER, bool RB, bool PROLONG, bool ZERO, int NHS, int RMODE,
+// R: rows per wave.  NHS: half-sweeps (0: 2 `sweeps`, a run-time count).
+template <int R, typename T, typename SO, typename SC, bool PER, bool RB, bool PROLONG, bool ZERO, int NHS, int RMODE,
           bool SOR, bool PLAIN>
 __device__ __forceinline__ void block_item(const BlockLaunch &a, const LevelDesc &L, const Seg &sx, const Seg &sy, int slot,
-                                           BlockShared<T> &sh)
+                                           int in_sel, int out_sel, int sweeps, BlockShared<T> &sh)
 {
+    static_assert(R % 2 == 0 && NHS % 2 == 0, "a wave's first row is even and sweeps are whole: static parities");
     using SOt = Stor<SO>;
     using SCt = Stor<SC>;
     using PO = typename SOt::Pair;
@@ -127,6 +128,8 @@ __device__ __forceinline__ void block_item(const BlockLaunch &a, const LevelDesc
     // ---- columns (c0 even) and rows of the lane, in the region and in the slice
     const int c0 = sx.r0 + 2 * lane;
     const int y0 = sy.r0 + wv * R;   // even
+    const bool dead = !PER && y0 >= H;        // (uniform) no row of this wave lies in the slice
+    const bool below = wv < kBlockWaves - 1 && (PER || y0 + R < H);   // (uniform) the next wave has some
     int x0, x1;
     bool in0 = true, in1 = true;       // Neumann: the column lies in the slice
     // colours alternate along the region's rows and columns (no wrap across an odd side)
@@ -156,7 +159,6 @@ __device__ __forceinline__ void block_item(const BlockLaunch &a, const LevelDesc
 
     // ---- loads: all rows at once
     const GDF_G SO *gb = (const GDF_G SO *)L.b;
-    int in_sel = a.in_sel, out_sel = a.out_sel;
     if constexpr (RB) {   // per-slice parity: the latest iterate sits in buffer cycles & 1
         if (a.cycles) {
             in_sel = uniform(a.cycles[(size_t)L.slice * a.cycles_stride]) & 1;
@@ -184,8 +186,16 @@ __device__ __forceinline__ void block_item(const BlockLaunch &a, const LevelDesc
         }
     };
     T b[R][2], u[R][2];
-    load_rows(gb, b);
-    if constexpr (!ZERO && RB) {
+    if (!dead) {
+        load_rows(gb, b);
+    } else {
+#pragma unroll
+        for (int r = 0; r < R; ++r) b[r][0] = b[r][1] = T(0);
+    }
+    if (ZERO || dead) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) u[r][0] = u[r][1] = T(0);
+    } else if constexpr (RB) {
         // rows stored by colour (LevelDesc): the lane's black pixel is element
         // x0 / 2 of half 1; the red one is dead (the first half-sweep overwrites it)
 #pragma unroll
@@ -193,16 +203,13 @@ __device__ __forceinline__ void block_item(const BlockLaunch &a, const LevelDesc
             u[r][(r & 1) ^ 1] = (T)ld<SO>(gu, (size_t)yw[r] * pitch + (pitch >> 1), (unsigned)x0 >> 1);
             u[r][r & 1] = T(0);
         }
-    } else if constexpr (!ZERO) {
-        load_rows(gu, u);
     } else {
-#pragma unroll
-        for (int r = 0; r < R; ++r) u[r][0] = u[r][1] = T(0);
+        load_rows(gu, u);
     }
 
     // ---- prolongation: cell-centred bilinear, 3/4 of the parent row plus 1/4 of
     // the next coarse row towards the fine row, then the same in x
-    if constexpr (PROLONG) {
+    if (PROLONG && !dead) {
         const GDF_G SC *ge = (const GDF_G SC *)L.ec;
         const int pc = L.pitch_c;
         if (regular) {
@@ -288,7 +295,7 @@ __device__ __forceinline__ void block_item(const BlockLaunch &a, const LevelDesc
     }
     // the level-0 mean is removed from the right-hand side (level 0), or its
     // children's share of it (a level 1 restricted from unshifted values)
-    {
+    if (!dead) {
         const T bsh = L.bshift ? (T)uniform_d(*L.bshift) : T(0);
         const T bsc = (a.raw_rhs && L.bshift_fine) ? T(4) * (T)uniform_d(*L.bshift_fine) : T(0);
         const T bsg = (bsh + bsc) * ivs;
@@ -318,11 +325,12 @@ __device__ __forceinline__ void block_item(const BlockLaunch &a, const LevelDesc
     // exchange of the waves' first and last rows: up[j] / dn[j] are column j of
     // the rows above and below the wave's (zero past the region's edge: only
     // halo rows, or rows without that coupling, read them).  Parity halves
-    // alternate, so one barrier separates the writes of one half-sweep from
+    // alternate with the colour, so one barrier separates the writes of one half-sweep from
     // its reads and from the next writes to the same half.
     auto exchange = [&](int p, bool both, int jf, int jl, T up[2], T dn[2]) {
         // jf: the column of the first row that the wave above reads; jl: of the last row
-        if (both) {
+        if (dead) {
+        } else if (both) {
             sh.x[p][0][0][wv][lane] = u[0][0];
             sh.x[p][0][1][wv][lane] = u[0][1];
             sh.x[p][1][0][wv][lane] = u[R - 1][0];
@@ -332,14 +340,15 @@ __device__ __forceinline__ void block_item(const BlockLaunch &a, const LevelDesc
             sh.x[p][1][0][wv][lane] = u[R - 1][jl];
         }
         __syncthreads();
-        if (both) {
+        if (dead) {
+        } else if (both) {
             up[0] = wv > 0 ? sh.x[p][1][0][wv - 1][lane] : T(0);
             up[1] = wv > 0 ? sh.x[p][1][1][wv - 1][lane] : T(0);
-            dn[0] = wv < kBlockWaves - 1 ? sh.x[p][0][0][wv + 1][lane] : T(0);
-            dn[1] = wv < kBlockWaves - 1 ? sh.x[p][0][1][wv + 1][lane] : T(0);
+            dn[0] = below ? sh.x[p][0][0][wv + 1][lane] : T(0);
+            dn[1] = below ? sh.x[p][0][1][wv + 1][lane] : T(0);
         } else {
             up[jl] = wv > 0 ? sh.x[p][1][0][wv - 1][lane] : T(0);
-            dn[jf] = wv < kBlockWaves - 1 ? sh.x[p][0][0][wv + 1][lane] : T(0);
+            dn[jf] = below ? sh.x[p][0][0][wv + 1][lane] : T(0);
         }
     };
     auto apply = [](const T4 &q, T vl, T vr, T vu, T vd, T bb) -> T {
@@ -347,20 +356,19 @@ __device__ __forceinline__ void block_item(const BlockLaunch &a, const LevelDesc
     };
     // (a regular half-sweep of colour c updates column (r & 1) ^ c of row r;
     // the first row is even, the last odd)
-#pragma unroll
-    for (int s = 1; s <= NHS; ++s) {
-        const int c = (s - 1) & 1;
+    auto half_sweep = [&](const int c, const bool first) __attribute__((always_inline)) {
         T up[2] = {T(0), T(0)}, dn[2] = {T(0), T(0)};
         if (PLAIN || regular) {
-            if (ZERO && !PROLONG && s == 1) {   // from zero: no neighbours yet
+            if (ZERO && !PROLONG && first) {   // from zero: no neighbours yet
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
                     const int j = (r & 1) ^ c;
                     u[r][j] = b[r][j];
                 }
-                continue;
+                return;
             }
-            exchange(s & 1, false, 1 ^ c, c, up, dn);
+            exchange(c, false, 1 ^ c, c, up, dn);
+            if (dead) return;
             auto sweep = [&](auto row) {
 #pragma unroll
                 for (int r = 0; r < R; ++r) {
@@ -372,7 +380,7 @@ __device__ __forceinline__ void block_item(const BlockLaunch &a, const LevelDesc
                     const T v = row(r, j, vl, vr, vu, vd);
                     // SOR: every half-sweep after the first moves its cells by kOmega
                     // times the Gauss-Seidel step (the first overwrites dead values)
-                    u[r][j] = SOR && s > 1 ? fma(T(kOmega), v - u[r][j], u[r][j]) : v;
+                    u[r][j] = SOR && !first ? fma(T(kOmega), v - u[r][j], u[r][j]) : v;
                 }
             };
             if constexpr (PLAIN) {
@@ -387,7 +395,7 @@ __device__ __forceinline__ void block_item(const BlockLaunch &a, const LevelDesc
         } else if constexpr (!PLAIN) {
             // an odd side wraps inside the region: colours per cell, all cells of
             // the colour updated from the values before the half-sweep
-            exchange(s & 1, true, 0, 0, up, dn);
+            exchange(c, true, 0, 0, up, dn);
             T p0 = up[0], p1 = up[1];   // the row above, before the half-sweep
 #pragma unroll
             for (int r = 0; r < R; ++r) {
@@ -403,6 +411,17 @@ __device__ __forceinline__ void block_item(const BlockLaunch &a, const LevelDesc
                 p0 = o0;
                 p1 = o1;
             }
+        }
+    };
+    if constexpr (NHS > 0) {
+#pragma unroll
+        for (int s = 0; s < NHS; ++s) half_sweep(s & 1, s == 0);
+    } else {
+        half_sweep(0, true);
+        half_sweep(1, false);
+        for (int s = 1; s < sweeps; ++s) {
+            half_sweep(0, false);
+            half_sweep(1, false);
         }
     }
 
@@ -432,7 +451,8 @@ __device__ __forceinline__ void block_item(const BlockLaunch &a, const LevelDesc
     if constexpr (RMODE != RES_NONE) {
         T up[2] = {T(0), T(0)}, dn[2] = {T(0), T(0)};
         const bool all = (RMODE & RES_NORM) != 0 || !(PLAIN || regular);
-        exchange((NHS + 1) & 1, all, 1, 0, up, dn);
+        exchange(0, all, 1, 0, up, dn);
+        if (dead && !(RMODE & RES_NORM)) return;   // (with norms there is a barrier below)
         double s2 = 0.0, s1 = 0.0;
         T prow = T(0);
         GDF_G SC *gc = (GDF_G SC *)L.bc;
@@ -533,9 +553,47 @@ __global__ __launch_bounds__(kBlockWaves *kWave, sizeof(T) == 4 ? 4 : 2) void bl
     const Seg sx = segment(PER, uniform(g.tx), L.W, kBlockCols, a.G, L.wxL);
     const Seg sy = segment(PER, uniform(g.ty), L.H, kBlockRows, a.G, L.wyL);
     if (sx.plain && sy.plain)
-        block_item<T, SO, SC, PER, RB, PROLONG, ZERO, NHS, RMODE, SOR, true>(a, L, sx, sy, slot, sh);
+        block_item<kR, T, SO, SC, PER, RB, PROLONG, ZERO, NHS, RMODE, SOR, true>(a, L, sx, sy, slot, a.in_sel, a.out_sel, 0,
+                                                                                 sh);
     else
-        block_item<T, SO, SC, PER, RB, PROLONG, ZERO, NHS, RMODE, SOR, false>(a, L, sx, sy, slot, sh);
+        block_item<kR, T, SO, SC, PER, RB, PROLONG, ZERO, NHS, RMODE, SOR, false>(a, L, sx, sy, slot, a.in_sel, a.out_sel, 0,
+                                                                                  sh);
+}
+
+// The coarse end of a Neumann V-cycle in one launch, one workgroup per slice: from
+// the first level that fits one region (kTailSide a side) down to the coarsest
+// and back up.  Each level is the pass above over its one tile; what one wave
+// writes and another reads goes through memory with a barrier between (the
+// workgroup's own CU, so no further fence).  A launch per pass costs 6.5 us on
+// levels this small, of which 3 are the launch and the item's table look-ups.
+template <typename T>
+__global__ __launch_bounds__(kBlockWaves *kWave, sizeof(T) == 4 ? 4 : 2) void tail_kernel(TailLaunch t)
+{
+    typedef typename LevelStor<T>::Coarse S;
+    __shared__ BlockShared<T> sh;
+    const BlockLaunch &a = t.a;
+    if (a.done && uniform(*a.done)) return;
+    const BItem &g = a.items[blockIdx.x];
+    const int lev = uniform(g.lev), l0 = uniform(g.tx), n = uniform(g.ty);   // first level's descriptor and number, levels
+    if (!uniform(a.active[uniform(a.levs[lev].slice)])) return;
+    auto pass = [&](auto prolong, auto rmode, int l, int in_sel, int out_sel, int sweeps) __attribute__((always_inline)) {
+        const LevelDesc L = uniform_level(a.levs[lev + l]);
+        const Seg sx{0, 0, L.W, false}, sy{0, 0, L.H, false};
+        constexpr bool P = decltype(prolong)::value;
+        if (L.H <= kBlockRows)
+            block_item<kR, T, S, S, false, false, P, !P, 0, decltype(rmode)::value, false, false>(
+                a, L, sx, sy, 0, in_sel, out_sel, sweeps, sh);
+        else
+            block_item<2 * kR, T, S, S, false, false, P, !P, 0, decltype(rmode)::value, false, false>(
+                a, L, sx, sy, 0, in_sel, out_sel, sweeps, sh);
+        __syncthreads();
+    };
+    using std::integral_constant;
+    for (int l = 0; l < n - 1; ++l)
+        pass(integral_constant<bool, false>{}, integral_constant<int, RES_RESTRICT>{}, l, 0, 0, t.sweeps[l0 + l]);
+    pass(integral_constant<bool, false>{}, integral_constant<int, RES_NONE>{}, n - 1, 0, 0, 2);
+    for (int l = n - 2; l >= 0; --l)
+        pass(integral_constant<bool, true>{}, integral_constant<int, RES_NONE>{}, l, 0, 1, t.sweeps[l0 + l]);
 }
 
 template <typename T, bool LEVEL0, bool PER, bool PROLONG, bool ZERO, int NHS, int RMODE>
@@ -635,6 +693,15 @@ hipError_t block_t(BlockKind k, bool periodic, bool level0, int sweeps, const Bl
 // half-sweep over memory), 12 x 1024 x 1200: 8.0 -> 0.55 ms a call.  Regions of
 // 128 rows (16 per wave; less halo, 120 registers) were slower on every stack
 // but the largest, and there not faster.
+hipError_t launch_tail(bool fp64, const TailLaunch &t, hipStream_t s)
+{
+    if (t.a.n_items <= 0) return hipSuccess;
+    const dim3 g((unsigned)t.a.n_items), blk(kBlockWaves * kWave);
+    if (fp64) hipLaunchKernelGGL(tail_kernel<double>, g, blk, 0, s, t);
+    else hipLaunchKernelGGL(tail_kernel<float>, g, blk, 0, s, t);
+    return hipGetLastError();
+}
+
 hipError_t launch_block_fine(bool zero, int sweeps, bool sor, bool fp64, const BlockLaunch &a, hipStream_t s)
 {
     if (fp64) return zero ? fine_sw<double, true>(sweeps, sor, a, s) : fine_sw<double, false>(sweeps, sor, a, s);

@@ -277,6 +277,16 @@ enum BlockKind {
 };
 // halo of a pass: cells that go stale per pass, rounded up to even
 constexpr int block_halo(int sweeps) { return 2 * sweeps + 2; }
+// The coarse levels of a slice from the first that is at most kTailSide a side, in
+// one workgroup (Neumann; at least two levels).  Items: lev the first level's
+// descriptor, tx its number, ty how many levels; sweeps per level number.
+constexpr int kTailSide = 128;
+static_assert(kTailSide <= kBlockCols && kTailSide <= 2 * kBlockRows, "a tail level is one region");
+struct TailLaunch {
+    BlockLaunch a;
+    int sweeps[kMaxLevels];
+};
+hipError_t launch_tail(bool fp64, const TailLaunch &t, hipStream_t s);
 // The fused finest pass (SK_FINE, SK_FINE_ZERO when zero) as blocks; halo
 // block_halo(sweeps).
 hipError_t launch_block_fine(bool zero, int sweeps, bool sor, bool fp64, const BlockLaunch &a, hipStream_t s);
