@@ -272,7 +272,10 @@ __device__ __forceinline__ void block_item(const BlockLaunch &a, const LevelDesc
         side_coef<T, PER>(PER ? x0 : c0, W, wxL, kxe, wx0, kl0, kr0);
         side_coef<T, PER>(PER ? x1 : c0 + 1, W, wxL, kxe, wx1, kl1, kr1);
         auto stencil = [&](bool in, T wx, T kl, T kr, T wy, T ku, T kd, T &d, T &i) -> T4 {
-            d = sig * wx * wy + wy * (kl + kr) + wx * (ku + kd);
+            // (a full cell with every neighbour takes the diagonal of PLAIN tiles to the
+            // last bit: the mean is removed alike in every tile, see below)
+            const bool full = wx == T(1) && wy == T(1) && kl == T(1) && kr == T(1) && ku == T(1) && kd == T(1);
+            d = full ? dg : sig * wx * wy + wy * (kl + kr) + wx * (ku + kd);
             i = in ? T(1) / d : T(0);
             return T4{wy * kl * i, wy * kr * i, wx * ku * i, wx * kd * i};
         };
@@ -301,7 +304,9 @@ __device__ __forceinline__ void block_item(const BlockLaunch &a, const LevelDesc
         const T bsg = (bsh + bsc) * ivs;
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            // the right-hand side is held over the diagonal
+            // the right-hand side is held over the diagonal (and the mean over it
+            // subtracted, as the strips do: its FP32 rounding is a constant of the
+            // whole slice)
             if constexpr (PLAIN) {
                 b[r][0] = fma(b[r][0], ivs, -bsg);
                 b[r][1] = fma(b[r][1], ivs, -bsg);
@@ -313,8 +318,8 @@ __device__ __forceinline__ void block_item(const BlockLaunch &a, const LevelDesc
                     i1 = sh.iv[row_class(r)][1][lane];
                 }
                 // (outside the slice: zero, whatever was loaded)
-                b[r][0] = in0 ? (b[r][0] - fma(bsc * wx0, wy, bsh)) * i0 : T(0);
-                b[r][1] = in1 ? (b[r][1] - fma(bsc * wx1, wy, bsh)) * i1 : T(0);
+                b[r][0] = in0 ? fma(b[r][0], i0, -(fma(bsc * wx0, wy, bsh) * i0)) : T(0);
+                b[r][1] = in1 ? fma(b[r][1], i1, -(fma(bsc * wx1, wy, bsh) * i1)) : T(0);
                 u[r][0] = in0 ? u[r][0] : T(0);
                 u[r][1] = in1 ? u[r][1] : T(0);
             }
