@@ -71,10 +71,11 @@ constexpr double kStallRatio = 0.6;
 // a persistent grid).  A block has no chain of dependent rows and fills the chip
 // with a small batch, but loads and computes 1.72 cells per cell owned, a strip
 // 1.48 once there are enough items for tall ones.  Per pass of 4 sweeps: 6 x 96 x
-// 80, 28 us as strips and 11 as blocks; a training step on 16 x 1024^2 2.73 and 2.39
-// ms; 24 x 901 x 1100 1.98 and 1.89 ms a call; 33 x 1021 x 1531 1.75 and 1.73 ms; 3 x
-// 4096^2 (50 Mpx) 1.62 and 1.64 ms; 64 x 2048^2 5.35 and 5.89 ms.
-constexpr double kFineBlockPx = 4.5e7;
+// 80, 28 us as strips and 11 as blocks.  Per call: a training step on 16 x 1024^2
+// 2.60 and 2.19 ms; 24 x 901 x 1100 1.81 and 1.68; 3 x 4096^2 1.57 and 1.51; 33 x
+// 1021 x 1531 1.66 and 1.61; 40 x 1536 x 1280 (79 Mpx) 3.53 and 3.49; 64 x 2048^2
+// (268 Mpx) 5.12 and 5.23; 96 of 512 to 4096 a side (510 Mpx) 10.7 and 11.5.
+constexpr double kFineBlockPx = 1e8;
 // The row-marching output pass from this many waves on: below it, the march of
 // 64 rows is longer (22 us) than the whole quad pass.
 constexpr long long kFinRowsMin = 256;
@@ -866,9 +867,9 @@ struct Run {
     // the unshifted values: 6 x 96 x 80, residual after one cycle 2e-3 instead of
     // 3e-4.)  The better first cycle makes more slices stop just inside tol after
     // three, where f is less accurate than after the fourth they used to take, so
-    // such a solve stops at 0.7 tol: f's error then stays at or below what it was on
-    // stacks at alpha 0.002 to 0.08, fewer slices miss tol in the exact check and
-    // run again, and 64 x 2048^2 takes 5.27 ms instead of 5.52 (0.5 tol: 5.43).
+    // such a solve stops at 0.6 tol: f's error then stays within 5% of what it was, or below, on
+    // 24 stacks at alpha 0.001 to 0.09, fewer slices miss tol in the exact check and
+    // run again, and 64 x 2048^2 takes 5.27 ms instead of 5.52 (at 0.5 tol 5.43).
     double loop_tol = 0.99;
 
     Run(const Plan &p, char *w, hipStream_t st_) : P(p), ws(w), s(st_)
@@ -1341,7 +1342,8 @@ gdf_status mixed_iterate(Run &R, int gs_dtype, const void *gs, int go_dtype, con
     ra.rhs = rhs;
     ra.io = R.io;
     ra.n_slices = P.n;
-    ra.n_tiles = P.n_tiles;
+    ra.rows = !P.periodic && march_rows(P);
+    ra.n_tiles = ra.rows ? P.n_ftiles : P.n_tiles;
     ra.levs = R.desc;
     ra.u64 = R.u64tab;
     ra.active = R.active;
@@ -1355,7 +1357,7 @@ gdf_status mixed_iterate(Run &R, int gs_dtype, const void *gs, int go_dtype, con
         ProfScope ps(PC_REFINE, 0.0, R.s, R.capturing);
         return P.periodic ? launch_prefine(ra, R.plaunch(), R.s) : launch_refine(ra, R.s);
     };
-    const int *rr_range = R.r_tiles;
+    const int *rr_range = ra.rows ? R.r_ftiles : R.r_tiles;
     const int steps = std::max(1, P.o.max_vc / P.o.inner);
     if (k0 == 1 && (r = R.finish(range_b, nullptr, part_b, FIN_CHECK, 0))) return r;
     const int saved_max = R.max_cycles;
@@ -2010,7 +2012,7 @@ static gdf_status fuse_stack_plain(const uint8_t *stack_all, int S_all, int H, i
         for (int z = 1; z < S; ++z)
             if ((long long)(P.g[z].off_b[1] - P.g[0].off_b[1]) != a.bc_slice_stride * z * P.csz) a.bc0 = nullptr;
     }
-    if (a.bc0) R.loop_tol = 0.7;
+    if (a.bc0) R.loop_tol = 0.6;
     a.part_bb = R.partd;
     a.part_b0 = R.partd2;
     a.part_bs = R.partd3;

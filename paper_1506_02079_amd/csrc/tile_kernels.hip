@@ -1129,9 +1129,171 @@ __global__ __launch_bounds__(256) void refine_kernel(RefineArgs a)
     if (threadIdx.x == 0) a.part_rr[c.tile] = t;
 }
 
+// The same by row marching (see finalize_kernel): the new iterate's rows y - 1, y,
+// y + 1 are held in registers, so every row of u64 and e is read once.  The quad
+// kernel reads each three times, from L2 where it is still there: 2 x 21504 x
+// 26624, 29 bytes per pixel (21 in the first step): 8.3 + 7.1 ms as quads, 6.8 + 5.0
+// (4.9 TB/s) marched.  FIRST: u64_in is zero.  RHS: the
+// right-hand side is a.rhs.
+template <typename TS, typename TO, bool RHS, bool FIRST>
+__global__ __launch_bounds__(64) void refine_rows_kernel(RefineArgs a)
+{
+    using VD = typename Vec4<double>::type;
+    using VF = typename Vec4<float>::type;
+    using V2 = typename Vec2<float>::type;
+    using VS = typename Vec4U<TS>::type;
+    using VO = typename Vec4U<TO>::type;
+    constexpr int Q = kFinQ;
+    const long long ft = xcd_tile(blockIdx.x, gridDim.x);
+    if (ft >= a.n_tiles) return;
+    const int si = find_fslice(a.io, a.n_slices, ft), lane = threadIdx.x;
+    if (!a.active[si]) {   // uniform
+        if (lane == 0) a.part_rr[ft] = 0.0;
+        return;
+    }
+    const RowBlock B = row_block(a.io, si, ft);
+    const SliceIO &P = a.io[si];
+    const int H = B.H, W = B.W, X0 = B.X0, Y0 = B.Y0, Y1 = B.Y1, x = B.x, xa = B.xa, xo = B.xo;
+    const bool tail = B.tail;
+    const double al = P.alpha;
+    const LevelDesc &L = a.levs[P.lev0];
+    const long long pl = L.pitch, pl2 = pl >> 1;
+    const GDF_GLOBAL float *e = (const GDF_GLOBAL float *)(a.e_sel ? L.u[1] : L.u[0]);
+    GDF_GLOBAL float *b = (GDF_GLOBAL float *)L.b;
+    const GDF_GLOBAL double *uin = (const GDF_GLOBAL double *)a.u64[a.in_sel * a.n_slices + si];
+    GDF_GLOBAL double *uout = (GDF_GLOBAL double *)a.u64[(a.in_sel ^ 1) * a.n_slices + si];
+    const long long pitch_s = RHS ? P.pitch_f : P.pitch_gs, pitch_go = P.pitch_go;
+    const GDF_GLOBAL TS *src = (const GDF_GLOBAL TS *)(RHS ? a.rhs : a.gs) + (RHS ? P.off_f : P.off_gs);
+    const GDF_GLOBAL TO *go = (const GDF_GLOBAL TO *)a.go + P.off_go;
+    // the wave's outer neighbour columns (lane 0: left, lane 63: right), clamped
+    const int xe = min(max(lane == 0 ? X0 - 1 : X0 + kFinCols, 0), W - 1);
+    const double ml = x > 0 ? 1.0 : 0.0, mr = x + 3 < W - 1 ? 1.0 : 0.0;
+    // raw loads of one row of the iterate (rows clamped into the slice; e is stored
+    // by colour, see finalize_kernel), and the new iterate's values from them
+    struct Row {
+        VD u;
+        V2 ev, od;
+        double ue;
+        float ee;
+    };
+    auto load_row = [&](int y, Row &q) {
+        const int yc = min(max(y, 0), H - 1);
+        const GDF_GLOBAL float *r0 = e + (long long)yc * pl;
+        q.ev = *reinterpret_cast<const GDF_GLOBAL V2 *>(r0 + ((yc & 1) ? pl2 : 0) + (xa >> 1));
+        q.od = *reinterpret_cast<const GDF_GLOBAL V2 *>(r0 + ((yc & 1) ? 0 : pl2) + (xa >> 1));
+        q.ee = r0[((xe + yc) & 1) * pl2 + (xe >> 1)];
+        if constexpr (!FIRST) {
+            q.u = *reinterpret_cast<const GDF_GLOBAL VD *>(uin + (long long)yc * pl + xa);
+            q.ue = uin[(long long)yc * pl + xe];
+        }
+    };
+    auto row_values = [&](const Row &q, double v[4], double &ve) {
+        v[0] = (double)q.ev.x;
+        v[1] = (double)q.od.x;
+        v[2] = (double)q.ev.y;
+        v[3] = (double)q.od.y;
+        ve = (double)q.ee;
+        if constexpr (!FIRST) {
+            v[0] += q.u.x;
+            v[1] += q.u.y;
+            v[2] += q.u.z;
+            v[3] += q.u.w;
+            ve += q.ue;
+        }
+        if (tail) fill_quad(B.nv, v);   // (past the row's end: its last pixel, so their difference is zero)
+    };
+    double un[4], uc[4], us[4], ue, t;
+    {
+        Row q;
+        load_row(Y0 - 1, q);   // (row -1: masked below)
+        row_values(q, un, t);
+        load_row(Y0, q);
+        row_values(q, uc, ue);
+    }
+    Row qr[Q];
+    VS qs[Q];
+    VO qo[Q];
+    auto issue = [&](int t, int slot) {
+        const int y = min(Y0 + t, Y1 - 1);
+        load_row(y + 1, qr[slot]);
+        qs[slot] = *reinterpret_cast<const GDF_GLOBAL VS *>(src + (long long)y * pitch_s + xo);
+        if constexpr (!RHS) qo[slot] = *reinterpret_cast<const GDF_GLOBAL VO *>(go + (long long)y * pitch_go + xo);
+    };
+#pragma unroll
+    for (int q = 0; q < Q - 1; ++q) issue(q, q);
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0) (see finalize_kernel)
+    double srr = 0.0;
+    const int n_rows = Y1 - Y0;
+    for (int tb = 0; tb < n_rows; tb += Q) {
+#pragma unroll
+        for (int k = 0; k < Q; ++k) {
+            const int r = tb + k;
+            issue(r + Q - 1, (k + Q - 1) % Q);
+            const int y = Y0 + r;
+            const double mu = y > 0 ? 1.0 : 0.0, md = y < H - 1 ? 1.0 : 0.0;   // uniform
+            const bool keep = r < n_rows && B.in;
+            double ue_next, bv[4];
+            row_values(qr[k], us, ue_next);
+            v4_to_d(tail ? shift_down(qs[k], B.d) : qs[k], bv);
+            if constexpr (!RHS) {
+                double o[4];
+                v4_to_d(tail ? shift_down(qo[k], B.d) : qo[k], o);
+#pragma unroll
+                for (int m = 0; m < 4; ++m) bv[m] = al * (bv[m] - o[m]);
+            }
+            double ul = wave_prev(uc[3]), ur = wave_next(uc[0]);
+            ul = lane == 0 ? ue : ul;
+            ur = lane == 63 ? ue : ur;
+            VF rv;
+            double rr = 0.0;
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                const double l = m == 0 ? ul : uc[m - 1], rt = m == 3 ? ur : uc[m + 1];
+                double acc = (m == 0 ? ml : 1.0) * (uc[m] - l);
+                acc = fma(m == 3 ? mr : 1.0, uc[m] - rt, acc);
+                acc = fma(mu, uc[m] - un[m], acc);
+                acc = fma(md, uc[m] - us[m], acc);
+                const double res = bv[m] - al * uc[m] - acc;
+                rv[m] = (float)res;
+                rr = fma(tail && m >= B.nv ? 0.0 : res, res, rr);
+            }
+            srr += keep ? rr : 0.0;
+            if (keep) {   // (arena rows are padded: whole quads may be stored past the row's end)
+                *reinterpret_cast<GDF_GLOBAL VD *>(uout + (long long)y * pl + xa) = VD{uc[0], uc[1], uc[2], uc[3]};
+                *reinterpret_cast<GDF_GLOBAL VF *>(b + (long long)y * pl + xa) = rv;
+            }
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                un[m] = uc[m];
+                uc[m] = us[m];
+            }
+            ue = ue_next;
+        }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) srr += __shfl_xor(srr, off);
+    if (lane == 0) a.part_rr[ft] = srr;
+}
+
+template <typename TS, typename TO, bool RHS>
+static hipError_t refine_rows(const RefineArgs &a, hipStream_t s)
+{
+    const dim3 g((unsigned)a.n_tiles);
+    if (a.first) hipLaunchKernelGGL((refine_rows_kernel<TS, TO, RHS, true>), g, dim3(64), 0, s, a);
+    else hipLaunchKernelGGL((refine_rows_kernel<TS, TO, RHS, false>), g, dim3(64), 0, s, a);
+    return hipGetLastError();
+}
+template <typename TS> static hipError_t refine_rows_t(const RefineArgs &a, hipStream_t s)
+{
+    if (a.rhs) return refine_rows<TS, uint8_t, true>(a, s);   // (g_o is not read)
+    return a.go_dtype == 0 ? refine_rows<TS, uint8_t, false>(a, s)
+         : a.go_dtype == 1 ? refine_rows<TS, float, false>(a, s) : refine_rows<TS, double, false>(a, s);
+}
+
 hipError_t launch_refine(const RefineArgs &a, hipStream_t s)
 {
     if (a.n_tiles <= 0) return hipSuccess;
+    if (a.rows) return a.gs_dtype == 2 ? refine_rows_t<double>(a, s) : refine_rows_t<float>(a, s);
     const dim3 g((unsigned)a.n_tiles), b(256);
     const bool s64 = a.gs_dtype == 2;
     switch (a.go_dtype) {
