@@ -827,7 +827,7 @@ hipError_t pinned_flags(int n, int *&out)
         int *nb = nullptr;
         const int want = std::max(n, 1024);
         const hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&nb), sizeof(int) * (size_t)want,
-                                           hipHostMallocDefault);
+                                           hipHostMallocPortable | hipHostMallocMapped);
         if (e != hipSuccess) return e;
         if (buf) (void)hipHostFree(buf);
         buf = nb;
@@ -836,6 +836,10 @@ hipError_t pinned_flags(int n, int *&out)
     out = buf;
     return hipSuccess;
 }
+
+// Number of the latest convergence check whose flags go to this thread's
+// page-locked buffer (pinned_flags).
+thread_local unsigned t_check = 0;
 
 struct Run {
     const Plan &P;
@@ -1030,9 +1034,17 @@ struct Run {
                       const double *pd2 = nullptr)
     {
         const bool in_loop = mode == FIN_CHECK && (pf || pd2);
+        unsigned *told = nullptr;
+        if (mode == FIN_CHECK && !capturing && !t_no_pinned) {
+            int *h = nullptr;
+            HIP_TRY(pinned_flags(P.n, h));
+            told = reinterpret_cast<unsigned *>(h);
+            t_check = (t_check + 1) & 0x3fffffffu;
+        }
+        flags_told = told;
         const double t = in_loop ? loop_tol * tol : tol;
         HIP_TRY(launch_finish(P.n, max_slots(range), range, pf, pd, pd2, mode, t, max_cycles, count, in_loop ? stall_ratio : 0.0, st,
-                              active, s));
+                              active, told, t_check, s));
         return GDF_OK;
     }
 
@@ -1100,8 +1112,33 @@ struct Run {
         return GDF_OK;
     }
 
+    // The flags after the latest device work.  The convergence check writes them to
+    // host memory itself and the host waits for its number to appear: a copy and a
+    // stream synchronisation after every cycle left the GPU idle for 20 us.
+    unsigned *flags_told = nullptr;   // the latest finish() was a check that tells the host
     gdf_status read_active(bool &any)
     {
+        if (flags_told) {
+            any = false;
+            for (int i = 0; i < P.n; ++i) {
+                volatile const unsigned *f = flags_told + i;
+                unsigned v = *f;
+                for (unsigned spin = 1; (v >> 1) != t_check; ++spin) {
+                    if ((spin & 0xfff) == 0) {
+                        const hipError_t q = hipStreamQuery(s);
+                        if (q == hipSuccess && (*f >> 1) != t_check)
+                            return set_err(GDF_EDEVICE, "internal: a convergence check did not report");
+                        if (q != hipSuccess && q != hipErrorNotReady) HIP_TRY(q);
+                    }
+                    __builtin_ia32_pause();
+                    v = *f;
+                }
+                active_host[i] = (v & 1u) != 0;
+                any |= active_host[i];
+            }
+            flags_told = nullptr;
+            return GDF_OK;
+        }
         int *h = nullptr;
         HIP_TRY(pinned_flags(P.n, h));
         HIP_TRY(hipMemcpyAsync(h, active, sizeof(int) * P.n, hipMemcpyDeviceToHost, s));
@@ -1167,9 +1204,11 @@ struct Run {
     // slice that stops improving has reached the working precision's floor and
     // is left to the FP64-refinement re-solve).
     std::vector<double> prev_exact;
+    std::vector<SliceState> states;   // as last read here; empty once more work is enqueued
     gdf_status resume_missed(bool &any)
     {
-        std::vector<SliceState> h(P.n);
+        std::vector<SliceState> &h = states;
+        h.resize(P.n);
         HIP_TRY(hipMemcpyAsync(h.data(), st, sizeof(SliceState) * P.n, hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
         if (prev_exact.empty()) prev_exact.assign(P.n, HUGE_VAL);
@@ -1187,8 +1226,10 @@ struct Run {
         if (any) {
             HIP_TRY(hipMemcpyAsync(active, act.data(), sizeof(int) * P.n, hipMemcpyHostToDevice, s));
             HIP_TRY(hipMemcpyAsync(only, act.data(), sizeof(int) * P.n, hipMemcpyHostToDevice, s));
+            HIP_TRY(hipStreamSynchronize(s));   // (act is pageable)
+            flags_told = nullptr;
+            states.clear();
         }
-        HIP_TRY(hipStreamSynchronize(s));
         return GDF_OK;
     }
 };
@@ -1243,12 +1284,16 @@ gdf_status upload_tables(const Plan &P, char *ws, const std::vector<SliceIO> &io
     return GDF_OK;
 }
 
+// known: the final states if the solve has read them already (else empty).
 gdf_status collect(const Plan &P, char *ws, hipStream_t s, gdf_slice_report *rep, double tol, int cycles_scale,
-                   std::vector<SliceState> *states = nullptr)
+                   std::vector<SliceState> *states = nullptr, std::vector<SliceState> known = {})
 {
-    std::vector<SliceState> h(P.n);
-    HIP_TRY(hipMemcpyAsync(h.data(), ws + P.off_state, sizeof(SliceState) * P.n, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    std::vector<SliceState> h = std::move(known);
+    if (h.empty()) {
+        h.resize(P.n);
+        HIP_TRY(hipMemcpyAsync(h.data(), ws + P.off_state, sizeof(SliceState) * P.n, hipMemcpyDeviceToHost, s));
+        HIP_TRY(hipStreamSynchronize(s));
+    }
     if (states) *states = h;
     gdf_status worst = GDF_OK;
     for (int i = 0; i < P.n; ++i) {
@@ -2064,7 +2109,7 @@ static gdf_status fuse_stack_plain(const uint8_t *stack_all, int S_all, int H, i
         if ((r = solve_body(R, x, BODY_REST))) return r;
     }
     std::vector<SliceState> h;
-    const gdf_status st = collect(P, ws, s, report, tol, mixed ? o.inner : 1, &h);
+    const gdf_status st = collect(P, ws, s, report, tol, mixed ? o.inner : 1, &h, R.states);
     if (st != GDF_ENOCONV || o.prec != GDF_PREC_FP32) return st;
     // Slices left above tol at the FP32 floor are re-solved by FP64 refinement
     // from their g_s (FP32) and the stack: from the returned g_s when there is
@@ -2445,7 +2490,7 @@ static gdf_status solve_slices_plain(int n, const gdf_slice_desc *d, int gs_dtyp
         if ((r = solve_body(R, x, BODY_REST))) return r;
     }
     std::vector<SliceState> h;
-    const gdf_status st = collect(P, ws, s, report, tol, o.prec == GDF_PREC_MIXED ? o.inner : 1, &h);
+    const gdf_status st = collect(P, ws, s, report, tol, o.prec == GDF_PREC_MIXED ? o.inner : 1, &h, R.states);
     if (st == GDF_ENOCONV && o.prec == GDF_PREC_FP32)
         return escalate(n, d, gs_dtype, gs, go_dtype, go, bc, tol, f, o, workspace, ws_bytes, h, report, stream);
     return st;

@@ -133,10 +133,12 @@ enum FinishMode {
 // above tol) stops with state.stalled = 1 (the working precision's floor).
 // partials_d2 (with partials_d, FIN_CHECK): FP64 partial sums of r, giving
 // the constant-mode correction as the strip partials do.
+// host_flags (FIN_CHECK, may be null): host memory the device writes; slice s's
+// entry becomes 2 seq + its flag.
 hipError_t launch_finish(int n_slices, int max_slots, const int *range, const float2 *partials_f,
                          const double *partials_d, const double *partials_d2, int mode, double tol,
                          int max_cycles, int count_cycle, double stall_ratio, SliceState *state, int *active,
-                         hipStream_t s);
+                         unsigned *host_flags, unsigned seq, hipStream_t s);
 
 // FIN_BB, FIN_INIT and FIN_MEAN of one right-hand side in one launch.
 hipError_t launch_finish_rhs(int n_slices, int max_slots, const int *range, const double *pbb, const double *pb0,

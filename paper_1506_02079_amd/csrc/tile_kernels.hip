@@ -216,7 +216,8 @@ template <int NT>
 __global__ __launch_bounds__(NT) void finish_kernel(int n_slices, const int *range,
                                                     const float2 *pf, const double *pd, const double *pd2,
                                                     int mode, double tol, int max_cycles, int count_cycle,
-                                                    double stall_ratio, SliceState *st, int *active)
+                                                    double stall_ratio, SliceState *st, int *active,
+                                                    unsigned *host_flags, unsigned seq)
 {
     __shared__ double red[NT / 64];
     const int sidx = blockIdx.x;
@@ -251,7 +252,15 @@ __global__ __launch_bounds__(NT) void finish_kernel(int n_slices, const int *ran
         break;
     case FIN_CHECK:
     default:
-        if (!active[sidx]) return;   // frozen slice keeps its last state
+        // the flag for the host: one posted write, tagged with the check's number
+        auto tell = [&](unsigned v) {
+            if (host_flags)
+                __hip_atomic_store(host_flags + sidx, seq * 2u + v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        };
+        if (!active[sidx]) {   // frozen slice keeps its last state
+            tell(0u);
+            return;
+        }
         const double prev = S.rel;   // the previous check's (0 before the first)
         S.rr = sum;
         S.rel = S.bb > 0.0 ? sqrt(sum / S.bb) : sqrt(sum);
@@ -266,6 +275,7 @@ __global__ __launch_bounds__(NT) void finish_kernel(int n_slices, const int *ran
         S.shift = has_r ? rsum / (S.npx * S.alpha) : 0.0;
         if (!isfinite(sum)) S.status = 6;
         if (!isfinite(sum) || S.rel <= tol || S.cycles >= max_cycles) active[sidx] = 0;
+        tell(active[sidx] ? 1u : 0u);
         break;
     }
 }
@@ -310,15 +320,17 @@ hipError_t launch_finish_rhs(int n_slices, int max_slots, const int *range, cons
 hipError_t launch_finish(int n_slices, int max_slots, const int *range, const float2 *partials_f,
                          const double *partials_d, const double *partials_d2, int mode, double tol,
                          int max_cycles, int count_cycle, double stall_ratio, SliceState *state, int *active,
-                         hipStream_t s)
+                         unsigned *host_flags, unsigned seq, hipStream_t s)
 {
     if (n_slices <= 0) return hipSuccess;
     if (max_slots > kFinWide)
         hipLaunchKernelGGL(finish_kernel<1024>, dim3(n_slices), dim3(1024), 0, s, n_slices, range, partials_f,
-                           partials_d, partials_d2, mode, tol, max_cycles, count_cycle, stall_ratio, state, active);
+                           partials_d, partials_d2, mode, tol, max_cycles, count_cycle, stall_ratio, state, active,
+                           host_flags, seq);
     else
         hipLaunchKernelGGL(finish_kernel<256>, dim3(n_slices), dim3(256), 0, s, n_slices, range, partials_f,
-                           partials_d, partials_d2, mode, tol, max_cycles, count_cycle, stall_ratio, state, active);
+                           partials_d, partials_d2, mode, tol, max_cycles, count_cycle, stall_ratio, state, active,
+                           host_flags, seq);
     return hipGetLastError();
 }
 
