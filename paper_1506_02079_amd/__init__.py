@@ -144,9 +144,17 @@ def _check(status, allow_noconv=False):
     raise GdfError(status, last_error())
 
 
+# the ctypes structures as numpy records (columns are filled and read at once: a
+# ctypes field access per slice is most of a call on hundreds of patches)
+_REPORT = np.dtype([("vcycles", "i4"), ("status", "i4"), ("rel_residual", "f8"), ("rel_residual_init", "f8")])
+_DESC = np.dtype([("H", "i4"), ("W", "i4"), ("alpha", "f8"), ("off_gs", "i8"), ("pitch_gs", "i8"), ("off_go", "i8"),
+                  ("pitch_go", "i8"), ("off_f", "i8"), ("pitch_f", "i8")])
+assert _REPORT.itemsize == ctypes.sizeof(SliceReport) and _DESC.itemsize == ctypes.sizeof(SliceDesc)
+
+
 def _report_list(rep, n):
-    return [dict(vcycles=rep[i].vcycles, status=rep[i].status, rel_residual=rep[i].rel_residual,
-                 rel_residual_init=rep[i].rel_residual_init) for i in range(n)]
+    return [dict(vcycles=v, status=st, rel_residual=r, rel_residual_init=r0)
+            for v, st, r, r0 in np.frombuffer(rep, dtype=_REPORT, count=n).tolist()]
 
 
 def _torch():
@@ -263,26 +271,33 @@ def fuse_stack(stack, alpha, bc="neumann", tol=1e-6, sigma_xy=1.0, sigma_z=3.0,
 # ---------------------------------------------------------------- solve_slices
 
 def _descs(gs_list, go_list, f_list, alphas):
-    """Slice descriptors for lists of 2D tensors, offsets from each list's lowest address."""
+    """Slice descriptors for lists of 2D tensors, offsets from each list's lowest
+    address.  f_list: a list too, or one tensor that holds the slices one after
+    the other."""
     n = len(gs_list)
-    d = (SliceDesc * n)()
+    if len(alphas) < n:
+        raise IndexError("fewer alphas than slices")
+    rec = np.zeros(n, dtype=_DESC)
+    hw = np.array([t.shape for t in gs_list], dtype=np.int64).reshape(n, 2)
+    rec["H"], rec["W"], rec["alpha"] = hw[:, 0], hw[:, 1], alphas[:n]
     bases = []
-    for lst in (gs_list, go_list, f_list):
-        base = min(t.data_ptr() for t in lst)
-        bases.append(base)
-    for i in range(n):
-        H, W = gs_list[i].shape
-        d[i].H, d[i].W, d[i].alpha = H, W, float(alphas[i])
-        for k, (lst, name) in enumerate(((gs_list, "gs"), (go_list, "go"), (f_list, "f"))):
-            t = lst[i]
-            if t.stride(1) != 1:
-                raise ValueError("slices must have unit column stride")
-            diff = t.data_ptr() - bases[k]
-            if diff % t.element_size():
-                raise ValueError("misaligned slice buffer")
-            setattr(d[i], "off_" + name, diff // t.element_size())
-            setattr(d[i], "pitch_" + name, t.stride(0))
-    return d, bases
+    for lst, name in ((gs_list, "gs"), (go_list, "go"), (f_list, "f")):
+        if not isinstance(lst, (list, tuple)):
+            px = hw[:, 0] * hw[:, 1]
+            rec["off_" + name], rec["pitch_" + name] = np.cumsum(px) - px, hw[:, 1]
+            bases.append(lst.data_ptr())
+            continue
+        ptr = np.array([t.data_ptr() for t in lst], dtype=np.uint64)
+        stride = np.array([t.stride() for t in lst], dtype=np.int64).reshape(n, 2)
+        if (stride[:, 1] != 1).any():
+            raise ValueError("slices must have unit column stride")
+        diff = (ptr - ptr.min()).astype(np.int64)
+        size = lst[0].element_size()
+        if (diff % size).any():
+            raise ValueError("misaligned slice buffer")
+        rec["off_" + name], rec["pitch_" + name] = diff // size, stride[:, 0]
+        bases.append(int(ptr.min()))
+    return (SliceDesc * n).from_buffer(rec), bases
 
 
 def solve_slices(g_s, g_o, alpha, bc="neumann", tol=1e-6, precision="fp32", out_dtype=None,
@@ -300,9 +315,9 @@ def solve_slices(g_s, g_o, alpha, bc="neumann", tol=1e-6, precision="fp32", out_
         raise ValueError("g_s and g_o must have the same number of slices")
     if not as_list and g_s.shape != g_o.shape:
         raise ValueError("g_s and g_o shapes differ")
-    for a, b in zip(gs_list, go_list):
-        if a.shape != b.shape or a.dim() != 2:
-            raise ValueError("each slice pair must be 2D with equal shapes")
+    shapes = [t.shape for t in gs_list]
+    if shapes != [t.shape for t in go_list] or any(len(v) != 2 for v in shapes):
+        raise ValueError("each slice pair must be 2D with equal shapes")
     _require_cuda(*gs_list, *go_list)
     gdt = {gs_list[0].dtype}
     if len({t.dtype for t in gs_list}) != 1 or len({t.dtype for t in go_list}) != 1:
@@ -314,16 +329,11 @@ def solve_slices(g_s, g_o, alpha, bc="neumann", tol=1e-6, precision="fp32", out_
     fdt = torch.float64 if od == DTYPE_F64 else torch.float32
     dev = gs_list[0].device
     if as_list:
-        tot = sum(t.numel() for t in gs_list)
-        flat = torch.empty(tot, dtype=fdt, device=dev)
-        f_list, off = [], 0
-        for t in gs_list:
-            f_list.append(flat[off:off + t.numel()].view(t.shape))
-            off += t.numel()
+        px = [v[0] * v[1] for v in shapes]
+        f_all = torch.empty(sum(px), dtype=fdt, device=dev)
     else:
         f_all = torch.empty(g_s.shape, dtype=fdt, device=dev)
-        f_list = list(f_all.unbind(0))
-    d, bases = _descs(gs_list, go_list, f_list, alphas)
+    d, bases = _descs(gs_list, go_list, f_all, alphas)
     L = lib()
     ws = L.gdf_solve_workspace_size(n, d, ctypes.byref(o))
     if ws == 0:
@@ -335,14 +345,18 @@ def solve_slices(g_s, g_o, alpha, bc="neumann", tol=1e-6, precision="fp32", out_
                                                          _dtype_code(go_list[0]), bases[1], BC[bc], float(tol),
                                                          bases[2], ctypes.byref(o), work.data_ptr(), ws, rep,
                                                          _stream(dev)),
-                             [work, *gs_list, *go_list, *f_list])
+                             [work, *gs_list, *go_list, f_all])
     else:
         st = L.solve_slices(n, d, _dtype_code(gs_list[0]), bases[0], _dtype_code(go_list[0]),
                             bases[1], BC[bc], float(tol), bases[2], ctypes.byref(o),
                             work.data_ptr(), ws, rep, _stream(dev))
     _check(st, allow_noconv)
     del gdt
-    return (f_list if as_list else f_all), _report_list(rep, n)
+    if not as_list:
+        return f_all, _report_list(rep, n)
+    # (one view per slice: as_strided is a third of a slice and a view)
+    offs = np.cumsum([0] + px).tolist()
+    return [f_all.as_strided(hw, (hw[1], 1), k) for hw, k in zip(shapes, offs)], _report_list(rep, n)
 
 
 def solve_slices_backward(grad_f, f, g_s, alpha, bc="neumann", tol=1e-6, precision=None, nu=0,
