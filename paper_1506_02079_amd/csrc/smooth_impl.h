@@ -72,27 +72,31 @@ __device__ __forceinline__ uint32_t load_raw_dword(const uint8_t *src, long long
     return v;
 }
 
-// Whether a stack takes the fixed-offset dword loads: rows 4-byte aligned and a
-// multiple of 4 wide (every dword whole), and a raw tile window small enough
-// for 32-bit offsets.
-inline bool smooth_fast_loads(const SmoothArgs &a)
+// How a stack's raw tiles are read.  LOAD_FIXED: rows 4-byte aligned and a multiple
+// of 4 wide, so every dword is whole: buffer loads at fixed per-thread offsets.
+// LOAD_ANY: any alignment and any width of at least 4, by dword loads that start on
+// any byte; where a row ends inside a dword the row's last four bytes are loaded
+// and shifted (tiles at the slice's edges only).  33 x 1021 x 1531, which took the
+// byte loads: 387 -> 245 us.  LOAD_BYTES: narrower slices.  All but the last need a raw
+// tile window small enough for 32-bit offsets.
+enum SmoothLoad { LOAD_BYTES, LOAD_FIXED, LOAD_ANY };
+inline SmoothLoad smooth_load(const SmoothArgs &a)
 {
     const bool aligned = ((a.pitch_row & 3) == 0) && ((a.pitch_slice & 3) == 0) &&
                          ((reinterpret_cast<uintptr_t>(a.stack) & 3) == 0);
-    return aligned && (a.W & 3) == 0 && a.pitch_row * kRawHMax < 0x7fffffffLL;
+    if (a.W < 4 || a.pitch_row * kRawHMax >= 0x7fffffffLL) return LOAD_BYTES;
+    return aligned && (a.W & 3) == 0 ? LOAD_FIXED : LOAD_ANY;
 }
 
 // RT: compile-time in-plane tap radius (>= the true radius; taps beyond it
-// carry zero weight), RZ: cross-slice tap radius.  FAST: the stack takes the
-// fixed-offset dword loads (smooth_fast_loads); otherwise raw tiles are read
-// byte by byte where a dword is not whole.  ROBUST (FP32): the robust
+// carry zero weight), RZ: cross-slice tap radius.  LOAD: see SmoothLoad.  ROBUST (FP32): the robust
 // cross-slice average of "Extensions and Applications" (values more than two
 // weighted standard deviations from the window's weighted mean left out).
 // Plain FP32 instances keep four waves per SIMD (two workgroups per CU); FP64
 // and robust ones need more registers than that allows.  RANGE: only the
 // output slices [a.z_lo, a.z_hi) are computed and stored (a uniform test per
 // step; without it the march has none).
-template <typename T, int RZ, int RT, bool FAST, bool ROBUST, bool RANGE>
+template <typename T, int RZ, int RT, SmoothLoad LOAD, bool ROBUST, bool RANGE>
 __global__ __launch_bounds__(kSThreads, ((sizeof(T) == 4 && !ROBUST) ? 4 : 1)) void smooth_kernel(SmoothArgs a)
 {
     constexpr int NZ = 2 * RZ + 1;     // register ring of blurred planes
@@ -159,9 +163,10 @@ __global__ __launch_bounds__(kSThreads, ((sizeof(T) == 4 && !ROBUST) ? 4 : 1)) v
     const long long nparts = (long long)a.tiles_x * a.tiles_y;   // one partial per tile
 
     uint32_t pf[kPrefetch];   // raw tile of the next input slice, in flight
-    // FAST: each thread loads the same raw dwords of every slice; their offsets
-    // in the tile's row window are fixed per thread (kNoLane outside the slice:
-    // the load reads zero).
+    // Each thread loads the same raw dwords of every slice; their offsets in the
+    // tile's row window are fixed per thread.  LOAD_FIXED: kNoLane outside the
+    // slice (the load reads zero); LOAD_ANY: always a valid address, and commit
+    // corrects the values in tiles whose window leaves the slice (`edge`).
     const int gy0 = max(Y0 - RH, 0), gy1 = min(Y0 + kSTY + RH, H);   // the window's rows
     unsigned voff[kPrefetch];
 #pragma unroll
@@ -170,10 +175,14 @@ __global__ __launch_bounds__(kSThreads, ((sizeof(T) == 4 && !ROBUST) ? 4 : 1)) v
         const int r = e / kRawDw, c = e - r * kRawDw;
         const int gy = Y0 - RH + r, gx = X0 - 8 + 4 * c;   // gx: a multiple of 4
         const bool in = e < n_dw && gy >= 0 && gy < H && gx >= 0 && gx < W;
-        voff[q] = in ? (unsigned)((gy - gy0) * a.pitch_row + gx) : kNoLane;
+        if constexpr (LOAD == LOAD_ANY)
+            voff[q] = in ? (unsigned)((gy - gy0) * a.pitch_row + min(gx, W - 4)) : 0u;
+        else
+            voff[q] = in ? (unsigned)((gy - gy0) * a.pitch_row + gx) : kNoLane;
     }
+    const bool edge = X0 < 8 || X0 + kRawW - 8 > W || Y0 < RH || Y0 + kSTY + RH > H;   // uniform
     auto issue = [&](int zi) {
-        if constexpr (FAST) {
+        if constexpr (LOAD == LOAD_FIXED) {
             // unconditional: a load under a branch would be waited for where the
             // paths join, right after its issue.  Past the stack the window is
             // empty (the loads read zero, and the slot is never read).
@@ -184,6 +193,16 @@ __global__ __launch_bounds__(kSThreads, ((sizeof(T) == 4 && !ROBUST) ? 4 : 1)) v
             const Rsrc rs = make_rsrc(a.stack + (long long)zc * a.pitch_slice + (long long)gy0 * a.pitch_row, nb);
 #pragma unroll
             for (int q = 0; q < kPrefetch; ++q) pf[q] = Buf<unsigned>::ld(rs, voff[q], 0);
+            return;
+        }
+        if constexpr (LOAD == LOAD_ANY) {
+            // (unconditional too; past the stack the last slice again, never read)
+            typedef uint32_t U32 __attribute__((aligned(1)));
+            const uint8_t *base = a.stack + (long long)min(zi, S - 1) * a.pitch_slice + (long long)gy0 * a.pitch_row;
+            const __attribute__((address_space(1))) uint8_t *gb = (const __attribute__((address_space(1))) uint8_t *)base;
+#pragma unroll
+            for (int q = 0; q < kPrefetch; ++q)
+                pf[q] = *reinterpret_cast<const __attribute__((address_space(1))) U32 *>(gb + voff[q]);
             return;
         }
 #pragma unroll
@@ -201,7 +220,14 @@ __global__ __launch_bounds__(kSThreads, ((sizeof(T) == 4 && !ROBUST) ? 4 : 1)) v
 #pragma unroll
         for (int q = 0; q < kPrefetch; ++q) {
             const int e = tid + q * kSThreads;
-            if (e < n_dw) ring_raw[zi % NRAW][e] = pf[q];
+            uint32_t v = pf[q];
+            if constexpr (LOAD == LOAD_ANY)
+                if (edge) {
+                    const int r = e / kRawDw, gy = Y0 - RH + r, gx = X0 - 8 + 4 * (e - r * kRawDw);
+                    const bool in = gy >= 0 && gy < H && gx >= 0 && gx < W;
+                    v = in ? v >> (8 * max(gx - (W - 4), 0)) : 0u;
+                }
+            if (e < n_dw) ring_raw[zi % NRAW][e] = v;
         }
     };
     // raw byte at tile-local raw row r (row 0 = Y0 - RH) and byte column c (x = X0 - 8 + c)
@@ -485,22 +511,24 @@ __global__ __launch_bounds__(kSThreads, ((sizeof(T) == 4 && !ROBUST) ? 4 : 1)) v
 
 // Launch one (precision, radius) instance; defined per cross-slice radius in
 // the smooth_rz*.hip translation units so they compile in parallel.
-template <typename T, int RZ, int RT, bool ROBUST, bool RANGE>
-hipError_t smooth_launch_r(const SmoothArgs &a, hipStream_t s)
+template <typename T, int RZ, int RT, SmoothLoad LOAD, bool ROBUST, bool RANGE>
+hipError_t smooth_go(const SmoothArgs &a, hipStream_t s)
 {
-    if (smooth_fast_loads(a))
-        hipLaunchKernelGGL((smooth_kernel<T, RZ, RT, true, ROBUST, RANGE>), dim3(a.tiles_x * a.tiles_y),
-                           dim3(kSThreads), 0, s, a);
-    else
-        hipLaunchKernelGGL((smooth_kernel<T, RZ, RT, false, ROBUST, RANGE>), dim3(a.tiles_x * a.tiles_y),
-                           dim3(kSThreads), 0, s, a);
+    hipLaunchKernelGGL((smooth_kernel<T, RZ, RT, LOAD, ROBUST, RANGE>), dim3(a.tiles_x * a.tiles_y), dim3(kSThreads), 0,
+                       s, a);
     return hipGetLastError();
 }
 template <typename T, int RZ, int RT, bool ROBUST>
 hipError_t smooth_launch(const SmoothArgs &a, hipStream_t s)
 {
-    if (a.z_lo == 0 && a.z_hi == a.S) return smooth_launch_r<T, RZ, RT, ROBUST, false>(a, s);
-    return smooth_launch_r<T, RZ, RT, ROBUST, true>(a, s);
+    const SmoothLoad m = smooth_load(a);
+    // (the byte loads serve every radius and range with the widest instance)
+    if (m == LOAD_BYTES) return smooth_go<T, RZ, kMaxRxy, LOAD_BYTES, ROBUST, true>(a, s);
+    if (a.z_lo == 0 && a.z_hi == a.S)
+        return m == LOAD_FIXED ? smooth_go<T, RZ, RT, LOAD_FIXED, ROBUST, false>(a, s)
+                               : smooth_go<T, RZ, RT, LOAD_ANY, ROBUST, false>(a, s);
+    return m == LOAD_FIXED ? smooth_go<T, RZ, RT, LOAD_FIXED, ROBUST, true>(a, s)
+                           : smooth_go<T, RZ, RT, LOAD_ANY, ROBUST, true>(a, s);
 }
 
 // All instances for one cross-slice radius RZ.
