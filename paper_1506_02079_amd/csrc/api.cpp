@@ -1420,6 +1420,7 @@ gdf_status mixed_iterate(Run &R, int gs_dtype, const void *gs, int go_dtype, con
         ra.in_sel = (k - 1) & 1;
         ra.e_sel = P.periodic ? 0 : P.o.inner & 1;
         HIP_TRY(refine());
+        R.raw_rhs_l1 = ra.rows;   // (restricted to level 1 as well; mixed hierarchies remove no mean)
         if ((r = R.finish(rr_range, nullptr, R.partd, FIN_CHECK, 1))) return r;
     }
     R.max_cycles = saved_max;
@@ -2049,15 +2050,15 @@ static gdf_status fuse_stack_plain(const uint8_t *stack_all, int S_all, int H, i
             return set_err(GDF_EDEVICE, "internal: non-uniform arena layout of a stack");
     a.b_pitch = P.g[0].pitch[0];
     // FP32 hierarchy: the smoothing pass also restricts b_u to level 1, so the
-    // solve's first pass has nothing left to do
-    if (!P.fp64 && !mixed && !periodic && P.g[0].nlev >= 2 && P.csz == 2) {
+    // solve's first pass (mixed: that of the first inner solve) has nothing left to do
+    if (!P.fp64 && !periodic && P.g[0].nlev >= 2 && P.csz == 2) {
         a.bc0 = ws + P.off_arena + P.g[0].off_b[1];
         a.bc_slice_stride = S > 1 ? (long long)((P.g[1].off_b[1] - P.g[0].off_b[1]) / P.csz) : 0;
         a.bc_pitch = P.g[0].pitch[1];
         for (int z = 1; z < S; ++z)
             if ((long long)(P.g[z].off_b[1] - P.g[0].off_b[1]) != a.bc_slice_stride * z * P.csz) a.bc0 = nullptr;
     }
-    if (a.bc0) R.loop_tol = 0.6;
+    if (a.bc0 && !mixed) R.loop_tol = 0.6;
     a.part_bb = R.partd;
     a.part_b0 = R.partd2;
     a.part_bs = R.partd3;

@@ -216,7 +216,8 @@ struct RefineArgs {
                              // alpha (g_s - g_o) -- the adjoint system A lambda = grad_f
     const SliceIO *io;
     int n_slices;
-    bool rows;               // by row marching (as in launch_finalize)
+    bool rows;               // by row marching (as in launch_finalize); then r is restricted
+                             // to level 1's right-hand side as well
     long long n_tiles;
     const LevelDesc *levs;   // FP32 hierarchy
     double *const *u64;      // [2][n_slices] device table of FP64 iterates (pitch = level-0 pitch)

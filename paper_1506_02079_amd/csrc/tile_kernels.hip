@@ -1145,7 +1145,9 @@ __global__ __launch_bounds__(256) void refine_kernel(RefineArgs a)
 // y + 1 are held in registers, so every row of u64 and e is read once.  The quad
 // kernel reads each three times, from L2 where it is still there: 2 x 21504 x
 // 26624, 29 bytes per pixel (21 in the first step): 8.3 + 7.1 ms as quads, 6.8 + 5.0
-// (4.9 TB/s) marched.  FIRST: u64_in is zero.  RHS: the
+// (4.9 TB/s) marched.  It also restricts the residual to level 1, whose cells are
+// two columns of a lane by two consecutive rows: the solve's own restriction pass
+// read it again (4.5 bytes per pixel, 1.1 ms there).  FIRST: u64_in is zero.  RHS: the
 // right-hand side is a.rhs.
 template <typename TS, typename TO, bool RHS, bool FIRST>
 __global__ __launch_bounds__(64) void refine_rows_kernel(RefineArgs a)
@@ -1236,6 +1238,13 @@ __global__ __launch_bounds__(64) void refine_rows_kernel(RefineArgs a)
     __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0) (see finalize_kernel)
     double srr = 0.0;
     const int n_rows = Y1 - Y0;
+    // level 1's right-hand side (null without one): the sums of each cell's children
+    GDF_GLOBAL unsigned short *bc = (GDF_GLOBAL unsigned short *)L.bc;
+    const long long pc = L.pitch_c;
+    static_assert(kFinRows % 2 == 0 && Q % 2 == 0, "a block starts on an even row; row parities are static");
+    float c0 = 0.f, c1 = 0.f;   // the cells' first rows
+    typedef float F2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 BF2 __attribute__((ext_vector_type(2)));
     for (int tb = 0; tb < n_rows; tb += Q) {
 #pragma unroll
         for (int k = 0; k < Q; ++k) {
@@ -1273,6 +1282,15 @@ __global__ __launch_bounds__(64) void refine_rows_kernel(RefineArgs a)
             if (keep) {   // (arena rows are padded: whole quads may be stored past the row's end)
                 *reinterpret_cast<GDF_GLOBAL VD *>(uout + (long long)y * pl + xa) = VD{uc[0], uc[1], uc[2], uc[3]};
                 *reinterpret_cast<GDF_GLOBAL VF *>(b + (long long)y * pl + xa) = rv;
+                // (pixels past the row's end add nothing)
+                const float s0 = rv.x + (tail && B.nv < 2 ? 0.f : rv.y);
+                const float s1 = (tail && B.nv < 3 ? 0.f : rv.z) + (tail && B.nv < 4 ? 0.f : rv.w);
+                c0 = (k & 1) ? c0 + s0 : s0;
+                c1 = (k & 1) ? c1 + s1 : s1;
+                // (the last row may be the only one of its cells; rows of level 1 are padded)
+                if (bc && ((k & 1) || y == H - 1))
+                    *reinterpret_cast<GDF_GLOBAL unsigned *>(bc + (long long)(y >> 1) * pc + (xa >> 1)) =
+                        __builtin_bit_cast(unsigned, __builtin_convertvector((F2{c0, c1}), BF2));
             }
 #pragma unroll
             for (int m = 0; m < 4; ++m) {
