@@ -871,9 +871,7 @@ struct Run {
     // the unshifted values: 6 x 96 x 80, residual after one cycle 2e-3 instead of
     // 3e-4.)  The better first cycle makes more slices stop just inside tol after
     // three, where f is less accurate than after the fourth they used to take, so
-    // such a solve stops at 0.6 tol: f's error then stays within 5% of what it was, or below, on
-    // 24 stacks at alpha 0.001 to 0.09, fewer slices miss tol in the exact check and
-    // run again, and 64 x 2048^2 takes 5.27 ms instead of 5.52 (at 0.5 tol 5.43).
+    // such a solve stops earlier in the loop (fused_loop_tol).
     double loop_tol = 0.99;
 
     Run(const Plan &p, char *w, hipStream_t st_) : P(p), ws(w), s(st_)
@@ -1943,6 +1941,16 @@ gdf_status fuse_stack(const uint8_t *stack, int S, int H, int W, long long pitch
     });
 }
 
+// The in-loop stop of a solve whose smoothing restricted b, relative to tol.  An
+// error of f of e goes with a residual of about alpha e in the smooth modes, so the
+// weaker the screening the more f's error depends on where a slice stops; and
+// robust averaging is for stacks with damaged slices, whose smooth correction is
+// large.  Relative error of f over 24 stacks at alpha 0.001 to 0.09, against what
+// it was: at most 1.04 times at 0.6, 1.5 at 0.85 (alpha 0.006); from alpha 0.01 on it stays
+// below 9e-7 at 0.85 (1.02e-6 at 0.99).  64 x 2048^2 at alpha 0.01: 6.04 ms at 0.6, where
+// many slices take a fourth cycle, 5.63 at 0.85; 5.81 before.
+static double fused_loop_tol(double alpha, bool robust) { return alpha >= 0.01 && !robust ? 0.85 : 0.6; }
+
 // Smoothing arguments of a stack (taps, renormalisation tables, tiling); the
 // caller sets the outputs (b_u, level-1 right-hand side, g_s, partial sums).
 static SmoothArgs smooth_args(const uint8_t *stack, int S, int H, int W, long long pitch_row, long long pitch_slice,
@@ -2058,7 +2066,7 @@ static gdf_status fuse_stack_plain(const uint8_t *stack_all, int S_all, int H, i
         for (int z = 1; z < S; ++z)
             if ((long long)(P.g[z].off_b[1] - P.g[0].off_b[1]) != a.bc_slice_stride * z * P.csz) a.bc0 = nullptr;
     }
-    if (a.bc0 && !mixed) R.loop_tol = 0.6;
+    if (a.bc0 && !mixed) R.loop_tol = fused_loop_tol(alpha, o.robust);
     a.part_bb = R.partd;
     a.part_b0 = R.partd2;
     a.part_bs = R.partd3;

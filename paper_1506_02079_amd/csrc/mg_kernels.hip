@@ -12,10 +12,10 @@
 // sum of its children's residuals (area-integrated).  Prolongation is
 // cell-centred bilinear interpolation (weights 9/16, 3/16, 3/16, 1/16) with
 // mirrored coarse values at the slice edges.  The smoother is red-black
-// Gauss-Seidel; cell (y, x) is red when x + y is even.  Level 0 (unit cells)
-// runs a specialised update with unit coefficients.
+// Gauss-Seidel; cell (y, x) is red when x + y is even.
 //
-// The strip kernel is the hot path.  One wavefront owns a strip of 128
+// The strip kernel runs level 0 (unit cells) of large batches; block_kernels.hip
+// has the other levels.  One wavefront owns a strip of 128
 // columns (two adjacent columns per lane) and marches down its rows, keeping a
 // ring of rows in registers.  Successive half-sweeps are skewed by two rows
 // (stage s processes the row loaded 2s steps earlier), which is exactly the
@@ -82,11 +82,10 @@ template <bool PROLONG, int NHS, int RMODE, int QM = GDF_QUEUE_MAX> struct Strip
 // a finite throwaway value, and no row inside the cone ever reads one (the
 // cones are nested), so the owned rows come out exactly as in the guarded
 // variant.  Inside the cones every row is an interior row (unit vertical
-// couplings) on every level; the b ring holds b times the inverse diagonal, so
+// couplings); the b ring holds b times the inverse diagonal, so
 // an update is one fused multiply-add on the neighbour sum.  With interior
 // columns as well (VAR 1) the stencil is the same for every lane (unit
-// couplings, diagonal sigma + 4); at column edges it is per lane (masks and,
-// on coarse levels, the narrower last column).
+// couplings, diagonal sigma + 4); at column edges it is per lane (masks).
 // SO: storage of this level's arrays; SC: storage of the next coarser level's
 // (prolongation source, restriction target).  Arithmetic is in T.
 template <typename T, typename SO, typename SC, bool PROLONG, bool ZERO, int NHS, int RMODE, int VAR, bool SOR = false>
