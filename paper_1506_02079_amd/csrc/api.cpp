@@ -827,7 +827,7 @@ hipError_t pinned_flags(int n, int *&out)
         int *nb = nullptr;
         const int want = std::max(n, 1024);
         const hipError_t e = hipHostMalloc(reinterpret_cast<void **>(&nb), sizeof(int) * (size_t)want,
-                                           hipHostMallocPortable | hipHostMallocMapped);
+                                           hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent);
         if (e != hipSuccess) return e;
         if (buf) (void)hipHostFree(buf);
         buf = nb;
