@@ -68,7 +68,7 @@ def host_cpu_model():
 # the fused finest pass (FP32 level 0, bfloat16 coarse level): prolongation, no zero
 # start, residual norm + restriction, unit stencil, plain or over-relaxed; one
 # launch per pass
-FINE_KERNEL_RE = r"strip_kernel<float, float, unsigned short, true, false, \d+, 3, false(, (true|false))?>"
+FINE_KERNEL_RE = r"strip_kernel<float, float, unsigned short, true, false, \d+, 3(, (true|false))?>"
 MG_SRC = os.path.join(ROOT, "paper_1506_02079_amd", "csrc", "mg_kernels.hip")
 
 
