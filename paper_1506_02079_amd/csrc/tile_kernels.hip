@@ -849,7 +849,7 @@ __global__ __launch_bounds__(64) void finalize_kernel(const TO *go_, TF *f_, con
             issue(t + Q - 1, (k + Q - 1) % Q);
             const int y = Y0 + t;
             const double mu = y > 0 ? 1.0 : 0.0, md = y < H - 1 ? 1.0 : 0.0;   // uniform
-            const double wrow = (t < n_rows && in) ? 1.0 : 0.0;
+            const bool keep = t < n_rows && in;
             double bb[4], o[4];
             quad_d(qev[k], qod[k], us);
             v4_to_d(qb[k], bb);
@@ -868,12 +868,14 @@ __global__ __launch_bounds__(64) void finalize_kernel(const TO *go_, TF *f_, con
                 acc = fma(kr, uc[m] - r, acc);
                 acc = fma(mu, uc[m] - un[m], acc);
                 acc = fma(md, uc[m] - us[m], acc);
-                const double res = bb[m] - sg * (uc[m] + shift) - acc;
-                rr = fma(tail && m >= B.nv ? 0.0 : res, res, rr);
+                // (past the row's end b is row padding, which may hold anything, NaN too:
+                // taken out by selection, here and for lanes past it, not by a factor zero)
+                const double res = tail && m >= B.nv ? 0.0 : bb[m] - sg * (uc[m] + shift) - acc;
+                rr = fma(res, res, rr);
                 fv[m] = (TF)(o[m] + (uc[m] + shift));
             }
-            srr = fma(wrow, rr, srr);
-            if (t < n_rows && in) {
+            srr += keep ? rr : 0.0;
+            if (keep) {
                 GDF_GLOBAL TF *fp = f + off_f + (long long)y * pitch_f + x;
                 if (!tail || B.nv == 4) {
                     *reinterpret_cast<GDF_GLOBAL VF *>(fp) = fv;
@@ -1276,7 +1278,8 @@ __global__ __launch_bounds__(64) void refine_rows_kernel(RefineArgs a)
                 acc = fma(md, uc[m] - us[m], acc);
                 const double res = bv[m] - al * uc[m] - acc;
                 rv[m] = (float)res;
-                rr = fma(tail && m >= B.nv ? 0.0 : res, res, rr);
+                const double rs = tail && m >= B.nv ? 0.0 : res;
+                rr = fma(rs, rs, rr);
             }
             srr += keep ? rr : 0.0;
             if (keep) {   // (arena rows are padded: whole quads may be stored past the row's end)
