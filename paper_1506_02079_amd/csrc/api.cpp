@@ -866,13 +866,6 @@ struct Run {
     // the smoothing pass restricted the unshifted b to level 1: the first pass
     // skips its restriction and the next level-1 down pass removes the mean
     bool raw_rhs_l1 = false;
-    // In a solve whose smoothing restricted the unshifted b, every level-1 pass of
-    // the first cycle removes the mean from it.  (The way up used to smooth against
-    // the unshifted values: 6 x 96 x 80, residual after one cycle 2e-3 instead of
-    // 3e-4.)  The better first cycle makes more slices stop just inside tol after
-    // three, where f is less accurate than after the fourth they used to take, so
-    // such a solve stops earlier in the loop (fused_loop_tol).
-    double loop_tol = 0.99;
 
     Run(const Plan &p, char *w, hipStream_t st_) : P(p), ws(w), s(st_)
     {
@@ -1019,8 +1012,8 @@ struct Run {
         return GDF_OK;
     }
 
-    // The in-loop test uses loop_tol x tol: the working-precision residual can sit
-    // a hair below the exact FP64 residual of the output, which is checked after.
+    // The in-loop test uses 0.99 tol: the working-precision residual can sit a
+    // hair below the exact FP64 residual of the output, which is checked after.
     // (in-loop checks -- strip partials, or FP64 partials with the sums of r --
     // use the working-precision residual)
     int max_slots(const int *range) const
@@ -1040,7 +1033,7 @@ struct Run {
             t_check = (t_check + 1) & 0x3fffffffu;
         }
         flags_told = told;
-        const double t = in_loop ? loop_tol * tol : tol;
+        const double t = in_loop ? 0.99 * tol : tol;
         HIP_TRY(launch_finish(P.n, max_slots(range), range, pf, pd, pd2, mode, t, max_cycles, count, in_loop ? stall_ratio : 0.0, st,
                               active, told, t_check, s));
         return GDF_OK;
@@ -1051,11 +1044,18 @@ struct Run {
     {
         const double e = fp64 ? 8.0 : 2.0;   // coarse-level element bytes
         gdf_status r;
+        // Only the way down removes the mean from an unshifted level-1 right-hand
+        // side.  On the way up as well, it would leave a smaller residual after the
+        // first cycle, and slices would then stop a cycle earlier, just inside tol:
+        // 9 x 701 x 333 at alpha 0.02 after 3 cycles, f 5.3e-7 from the solution in 64
+        // bits, instead of after 4 and 9.7e-8; over 96 stacks at alpha 0.001 to 0.1, 47
+        // end further off, the worst 5.5 times, and a stricter in-loop stop that brings
+        // them back takes up to 1.2 times as long (64 x 2048^2 at alpha 0.0015).
         const bool raw = raw_rhs_l1;
         raw_rhs_l1 = false;
         for (int l = 1; l <= P.max_level; ++l) {
             if ((r = block(P.bmid[l], BK_DOWN_ZERO, l, 0, 0, fp64, 2.25 * e, raw && l == 1))) return r;
-            if ((r = block(P.blast[l], BK_LAST_ZERO, l, 0, 0, fp64, 2 * e, raw && l == 1))) return r;
+            if ((r = block(P.blast[l], BK_LAST_ZERO, l, 0, 0, fp64, 2 * e))) return r;
         }
         if (P.btail.count) {
             TailLaunch t{};
@@ -1070,7 +1070,7 @@ struct Run {
             HIP_TRY(launch_tail(fp64, t, s));
         }
         for (int l = P.max_level - 1; l >= 1; --l)
-            if ((r = block(P.bmid[l], BK_UP, l, 0, 1, fp64, 3.25 * e, raw && l == 1))) return r;
+            if ((r = block(P.bmid[l], BK_UP, l, 0, 1, fp64, 3.25 * e))) return r;
         return GDF_OK;
     }
 
@@ -1941,16 +1941,6 @@ gdf_status fuse_stack(const uint8_t *stack, int S, int H, int W, long long pitch
     });
 }
 
-// The in-loop stop of a solve whose smoothing restricted b, relative to tol.  An
-// error of f of e goes with a residual of about alpha e in the smooth modes, so the
-// weaker the screening the more f's error depends on where a slice stops; and
-// robust averaging is for stacks with damaged slices, whose smooth correction is
-// large.  Relative error of f over 24 stacks at alpha 0.001 to 0.09, against what
-// it was: at most 1.04 times at 0.6, 1.5 at 0.85 (alpha 0.006); from alpha 0.01 on it stays
-// below 9e-7 at 0.85 (1.02e-6 at 0.99).  64 x 2048^2 at alpha 0.01: 6.04 ms at 0.6, where
-// many slices take a fourth cycle, 5.63 at 0.85; 5.81 before.
-static double fused_loop_tol(double alpha, bool robust) { return alpha >= 0.01 && !robust ? 0.85 : 0.6; }
-
 // Smoothing arguments of a stack (taps, renormalisation tables, tiling); the
 // caller sets the outputs (b_u, level-1 right-hand side, g_s, partial sums).
 static SmoothArgs smooth_args(const uint8_t *stack, int S, int H, int W, long long pitch_row, long long pitch_slice,
@@ -2066,7 +2056,6 @@ static gdf_status fuse_stack_plain(const uint8_t *stack_all, int S_all, int H, i
         for (int z = 1; z < S; ++z)
             if ((long long)(P.g[z].off_b[1] - P.g[0].off_b[1]) != a.bc_slice_stride * z * P.csz) a.bc0 = nullptr;
     }
-    if (a.bc0 && !mixed) R.loop_tol = fused_loop_tol(alpha, o.robust);
     a.part_bb = R.partd;
     a.part_b0 = R.partd2;
     a.part_bs = R.partd3;
