@@ -1560,17 +1560,19 @@ size_t tuned_workspace(const std::vector<unsigned long long> &key, const gdf_sol
     for (int nu : tune_nus(base))
         for (int fs : tune_fine_sweeps(base, nu))
             for (int cs : tune_coarse_sweeps(base, nu))
-                for (int tr : tune_tiles(base)) {
-                    gdf_solve_opts c = base;
-                    c.autotune = 0;
-                    c.nu = nu;
-                    c.fine_sweeps = fs;
-                    c.coarse_sweeps = cs;
-                    c.tile_rows = tr;
-                    const size_t b = size_of(&c);
-                    if (b == 0) return 0;
-                    m = std::max(m, b);
-                }
+                for (int tr : tune_tiles(base))
+                    for (int la : tune_launches(base)) {   // (level 0 as blocks or as strips)
+                        gdf_solve_opts c = base;
+                        c.autotune = 0;
+                        c.nu = nu;
+                        c.fine_sweeps = fs;
+                        c.coarse_sweeps = cs;
+                        c.tile_rows = tr;
+                        c.launch_mode = la;
+                        const size_t b = size_of(&c);
+                        if (b == 0) return 0;
+                        m = std::max(m, b);
+                    }
     std::lock_guard<std::mutex> lk(g_wsz_mu);
     if (g_wsz.size() >= 64) g_wsz.erase(g_wsz.begin());
     g_wsz.emplace_back(key, m);
