@@ -1662,6 +1662,20 @@ gdf_status autotuned(const std::vector<unsigned long long> &key, const gdf_solve
     return call(&best);
 }
 
+// The largest count of 1 .. n that fits (0: none), for a fits() that holds up to some
+// count: a few plans are built, not one per slice.
+template <class Fits> size_t largest_fit(size_t n, Fits fits)
+{
+    if (n == 0 || fits(n)) return n;
+    size_t lo = 0, hi = n;
+    while (hi - lo > 1) {
+        const size_t mid = lo + (hi - lo) / 2;
+        if (fits(mid)) lo = mid;
+        else hi = mid;
+    }
+    return lo;
+}
+
 }  // namespace
 
 // ===================================================================== ABI
@@ -2144,12 +2158,10 @@ static gdf_status fuse_stack_plain(const uint8_t *stack_all, int S_all, int H, i
     a1.part_bb = a1.part_b0 = a1.part_bs = nullptr;
     for (size_t k = 0; k < todo.size();) {
         // (slices of one stack: any group of a size needs the same room)
-        size_t cnt = todo.size() - k;
-        while (cnt > 0) {
-            const size_t need = solve_workspace_plain((int)cnt, d.data(), &m);
-            if (need && cnt * gs1 + need <= ws_bytes) break;
-            cnt = cnt > 4 ? cnt / 2 : cnt - 1;
-        }
+        const size_t cnt = largest_fit(todo.size() - k, [&](size_t c) {
+            const size_t need = solve_workspace_plain((int)c, d.data(), &m);
+            return need && c * gs1 + need <= ws_bytes;
+        });
         if (cnt == 0) break;   // no room for one: they keep GDF_ENOCONV
         const std::vector<int> group(todo.begin() + k, todo.begin() + k + cnt);
         for (size_t i = 0; i < cnt; ++i) {
@@ -2329,21 +2341,20 @@ static gdf_status escalate_slices(const std::vector<int> &todo, const gdf_slice_
     const gdf_solve_opts m = escalation_call_opts(o);
     size_t k = 0;
     while (k < todo.size()) {
-        // the largest group that fits, halving from all that are left
+        // as many of the slices left, in order, as fit
         std::vector<gdf_slice_desc> g;
-        std::vector<int> idx;
-        for (size_t cnt = todo.size() - k; cnt > 0; cnt = cnt > 4 ? cnt / 2 : cnt - 1) {
-            g.clear();
-            for (size_t i = k; i < k + cnt; ++i) g.push_back(d[todo[i]]);
-            const size_t need = solve_workspace_plain((int)cnt, g.data(), &m);
-            if (need && need <= ws_bytes) break;
-            g.clear();
-        }
-        for (size_t i = 0; i < g.size(); ++i) idx.push_back(todo[k++]);
-        if (g.empty()) {   // this slice alone does not fit: it keeps GDF_ENOCONV
+        for (size_t i = k; i < todo.size(); ++i) g.push_back(d[todo[i]]);
+        const size_t cnt = largest_fit(g.size(), [&](size_t c) {
+            const size_t need = solve_workspace_plain((int)c, g.data(), &m);
+            return need && need <= ws_bytes;
+        });
+        if (cnt == 0) {   // this slice alone does not fit: it keeps GDF_ENOCONV
             ++k;
             continue;
         }
+        g.resize(cnt);
+        const std::vector<int> idx(todo.begin() + k, todo.begin() + k + cnt);
+        k += cnt;
         std::vector<gdf_slice_report> sub(g.size());
         const gdf_status r = solve_slices_plain((int)g.size(), g.data(), gs_dtype, gs, go_dtype, go, bc, tol, f,
                                                 &m, ws, ws_bytes, sub.data(), stream);
