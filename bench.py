@@ -45,12 +45,12 @@ def log(*a):
 
 def traffic_from_profile():
     """HBM bytes per launch of the fused finest pass from the committed
-    rocprofv3 counter summary, or None if the kernel source changed since."""
+    rocprofv3 counter summary, or None if the kernel's sources changed since."""
     path = os.path.join(ROOT, "profiles", "vcycle_fine_traffic.json")
     if not os.path.exists(path):
         return None
     rec = json.load(open(path))
-    if hashlib.sha256(open(MG_SRC, "rb").read()).hexdigest() != rec.get("mg_kernels_sha256"):
+    if fine_kernel_sha256() != rec.get("kernel_sources_sha256"):
         return None
     return rec.get("hbm_bytes_per_launch")
 
@@ -70,6 +70,16 @@ def host_cpu_model():
 # launch per pass
 FINE_KERNEL_RE = r"strip_kernel<float, float, unsigned short, true, false, \d+, 3(, (true|false))?>"
 MG_SRC = os.path.join(ROOT, "paper_1506_02079_amd", "csrc", "mg_kernels.hip")
+
+
+def fine_kernel_sha256():
+    """Hash of the fused finest pass's source and of every local header it includes
+    (storage types, lane shifts, buffer access, level layout, over-relaxation)."""
+    from paper_1506_02079_amd import build
+    h = hashlib.sha256()
+    for path in sorted(build._deps(MG_SRC, set()), key=os.path.basename):
+        h.update(os.path.basename(path).encode() + b"\0" + open(path, "rb").read())
+    return h.hexdigest()
 
 
 def _counter_rows(d):
@@ -98,7 +108,7 @@ def summarize_pmc(fetch_dir, write_dir, out_json, command):
     rec = {"kernel": "vcycle_fine (strip_kernel SK_FINE, FP32 with bfloat16 coarse level, over-relaxed "
                      "sweeps as the bench runs it; one launch per pass)",
            "workload": "fuse_stack 64 x 2048 x 2048, alpha 0.01, tol 1e-6",
-           "mg_kernels_sha256": hashlib.sha256(open(MG_SRC, "rb").read()).hexdigest(),
+           "kernel_sources_sha256": fine_kernel_sha256(),
            "hbm_read_bytes_per_launch": rd, "hbm_write_bytes_per_launch": wr,
            "hbm_bytes_per_launch": (rd + wr) if rd and wr else None,
            "counters": res, "command": command}
