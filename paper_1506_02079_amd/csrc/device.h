@@ -78,7 +78,12 @@ template <typename X, typename R> struct BufBits {   // 8- and 16-byte values
     __device__ static void st(X v, Rsrc r, unsigned vo, unsigned so)
     {
         if constexpr (sizeof(X) == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(R, v), r, (int)vo, (int)so, 0);
-        else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(R, v), r, (int)vo, (int)so, 0);
+        // A store of more than 8 bytes reads its data over several cycles.  Writing those
+        // registers right behind it needs wait states, which the compiler only inserts
+        // where no scalar register holds the offset: with one there, the last four of
+        // every 16 lanes stored what the next instruction had put into the register
+        // (now and then, in FP64 strips).  So the row offset goes into the lane's.
+        else __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(R, v), r, (int)(vo + so), 0, 0);
     }
 };
 template <> struct Buf<double> : BufBits<double, U2> {};
