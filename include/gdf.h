@@ -68,8 +68,8 @@ typedef enum {
     GDF_BC_PERIODIC = 1,   /* wrap-around (the paper's Fourier basis, Section III-B): the first
                               and last row and column of a slice are neighbours; a side of two
                               pixels couples them across both faces, a side of one has no
-                              coupling.  Solved by a multigrid of its own (plain per-level
-                              kernels); workspace sizes are the same for either boundary. */
+                              coupling.  Solved by a multigrid of its own (register-block
+                              passes on every level); workspace sizes are the same for either boundary. */
     GDF_BC_DIRICHLET = 2   /* boundary values are not specified by the method: GDF_EUNSUPPORTED */
 } gdf_bc;
 
@@ -89,12 +89,20 @@ typedef struct {
     int nu;            /* red-black Gauss-Seidel sweeps before and after each coarse
                           correction on the finest level: 1 or 2 (default 2) */
     int out_dtype;     /* GDF_F32 or GDF_F64 for f; 0 = F32 for FP32, F64 otherwise */
-    int use_graph;     /* 1: record the whole V-cycle schedule once as a hipGraph and
-                          replay it, with per-slice convergence flags on the device */
-    int tile_rows;     /* rows per level-0 strip work item (even, >= 16); 0 = 80, halved
-                          (down to 16) for batches too small to fill the GPU twice over */
+    int use_graph;     /* 1: record the V-cycle schedule once as a hipGraph and replay it,
+                          with per-slice convergence flags on the device.  With a report the
+                          graph holds the first 6 cycles (MIXED: 3 refinement steps) and
+                          the host continues slices that need more; without one it holds
+                          max_vcycles of them */
+    int tile_rows;     /* rows per level-0 strip work item (even, >= 16).  0: batches of up to
+                          100 Mpx run the fused finest passes as register blocks, larger ones
+                          as strips of 80 rows, halved (down to 16) where that leaves the GPU
+                          less than twice full.  Any other value keeps the strips, whatever
+                          the batch (Neumann; the other levels and the periodic multigrid
+                          are always blocks) */
     int inner_cycles;  /* MIXED: FP32 V-cycles per refinement step (default 3) */
-    int launch_mode;   /* gdf_launch_mode for the multigrid passes (default GDF_LAUNCH_GRID) */
+    int launch_mode;   /* gdf_launch_mode of the level-0 strips (default GDF_LAUNCH_GRID);
+                          GDF_LAUNCH_PERSISTENT keeps the strips as tile_rows does */
     int autotune;      /* 1: pick nu, fine_sweeps, coarse_sweeps, tile_rows and launch_mode by timing
                           candidate solves of this very call (see "Autotuning" below) */
     int fine_sweeps;   /* red-black sweeps in each fused finest-level pass (the post-sweeps
@@ -132,9 +140,9 @@ typedef struct {
 
 typedef enum {
     GDF_LAUNCH_DEFAULT = 0,     /* library default (GDF_LAUNCH_GRID) */
-    GDF_LAUNCH_GRID = 1,        /* one wavefront per work item: the grid covers the work list */
-    GDF_LAUNCH_PERSISTENT = 2   /* grid capped at the workgroups resident on the GPU at once;
-                                   each wavefront loops over the work list */
+    GDF_LAUNCH_GRID = 1,        /* strips: one wavefront per work item, the grid covers the list */
+    GDF_LAUNCH_PERSISTENT = 2   /* strips: grid capped at the workgroups resident on the GPU at
+                                   once; each wavefront loops over the list */
 } gdf_launch_mode;
 
 /* Per-slice outcome (host memory, filled when a report pointer is given). */
@@ -183,15 +191,18 @@ void gdf_release(void);
  * g_smooth_dev   optional output [S][H][W] contiguous (NULL to skip): I1 in
  *                FP32 (FP64 when precision is GDF_PREC_FP64).
  * report_host    optional [S] per-slice report.
- * With opts.use_graph the smoothing and the whole solve are captured as one
- * graph per (sizes, pointers, stream, options) and replayed, convergence
- * decided on the device: the call then waits for the device only to read the
- * report (cap opts.max_vcycles: the graph holds that many cycles, which
- * converged slices skip).  With use_graph and report_host NULL the call is
+ * With opts.use_graph the smoothing and the solve are captured as one graph
+ * per (sizes, pointers, stream, options) and replayed, convergence decided on
+ * the device.  With a report the graph holds the first 6 cycles (MIXED: 3
+ * refinement steps), which converged slices skip; the call then waits for the
+ * device, and the host issues what slices still above tol need beyond them,
+ * up to max_vcycles.  With use_graph and report_host NULL the call is
  * asynchronous: it returns GDF_OK once the work is enqueued on the stream,
- * without waiting; slices are not checked against tol on the host and
- * slices left at the FP32 floor are not re-solved (reading the report is
- * what decides both).  The workspace and buffers must stay valid until the
+ * without waiting, and the graph holds max_vcycles cycles (cap them: each
+ * launches its passes, which exit at once where nothing is left to do);
+ * slices are not checked against tol on the host and slices left at the FP32
+ * floor are not re-solved (reading the report is what decides both).  The
+ * workspace and buffers must stay valid until the
  * stream has run the work.
  * Returns GDF_OK when every slice reached tol.                              */
 size_t gdf_fuse_workspace_size(int S, int H, int W, const gdf_solve_opts *opts);
@@ -211,8 +222,8 @@ gdf_status fuse_stack(const uint8_t *stack_dev, int S, int H, int W, long long p
  * go_dtype/go    g_o buffer: GDF_U8, GDF_F32 or GDF_F64.
  * f_dev          output buffer, dtype opts.out_dtype.
  * Uneven batches run as one work list per multigrid level; with
- * opts.use_graph the schedule is captured once and replayed, and with
- * use_graph and report_host NULL the call is asynchronous (as fuse_stack).  */
+ * opts.use_graph the schedule is captured once and replayed, with or without
+ * a report as fuse_stack does.                                              */
 size_t gdf_solve_workspace_size(int n, const gdf_slice_desc *desc_host, const gdf_solve_opts *opts);
 
 gdf_status solve_slices(int n, const gdf_slice_desc *desc_host, int gs_dtype, const void *gs_dev,

@@ -217,11 +217,13 @@ def fuse_stack(stack, alpha, bc="neumann", tol=1e-6, sigma_xy=1.0, sigma_z=3.0,
     standard deviations from the window's weighted mean are left out).
     z_range=(z0, z1): solve only slices z0 .. z1 - 1 (the others only enter
     their cross-slice windows); f, g_smooth and the report then hold z1 - z0
-    slices.  use_graph=True: the whole schedule (smoothing and every V-cycle,
-    with the convergence test on the device) is captured once per shape,
-    pointers and options, then replayed; the host waits only for the report.
-    use_graph=True, wait=False: asynchronous; the call returns (f, None) once
-    the work is enqueued on the current stream (no report, no per-slice check).
+    slices.  use_graph=True: the schedule (smoothing and V-cycles, with the
+    convergence test on the device) is captured once per shape, pointers and
+    options, then replayed; the graph holds the first 6 cycles (mixed: 3
+    refinement steps), and the host continues slices that need more.
+    use_graph=True, wait=False: asynchronous, max_vcycles cycles in the graph; the
+    call returns (f, None) once the work is enqueued on the current stream (no
+    report, no per-slice check).
 
     Returns (f, report) or (f, report, g_smooth) with return_smooth=True.
     f has dtype float32 (fp32) or float64 (fp64 / mixed) unless out_dtype is given.

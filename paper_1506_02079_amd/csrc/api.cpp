@@ -71,10 +71,17 @@ constexpr double kStallRatio = 0.6;
 // a persistent grid).  A block has no chain of dependent rows and fills the chip
 // with a small batch, but loads and computes 1.72 cells per cell owned, a strip
 // 1.48 once there are enough items for tall ones.  Per pass of 4 sweeps: 6 x 96 x
-// 80, 28 us as strips and 11 as blocks.  Per call: a training step on 16 x 1024^2
-// 2.60 and 2.19 ms; 24 x 901 x 1100 1.81 and 1.68; 3 x 4096^2 1.57 and 1.51; 33 x
-// 1021 x 1531 1.66 and 1.61; 40 x 1536 x 1280 (79 Mpx) 3.53 and 3.49; 64 x 2048^2
-// (268 Mpx) 5.12 and 5.23; 96 of 512 to 4096 a side (510 Mpx) 10.7 and 11.5.
+// 80, 28 us as strips and 11 as blocks.  A fuse_stack call as blocks, over the same
+// as strips (FP32, alpha 0.01 and 0.002, plain and over-relaxed; mixed; FP64):
+//   17 Mpx (16 x 1024^2)   0.83 - 0.85   0.81   0.91
+//   42 Mpx (40 x 1024^2)   0.96 - 0.98   0.95   0.95
+//   84 Mpx (80 x 1024^2)   0.97 - 1.00   0.97   0.95
+//   96 Mpx (23 x 2048^2)   1.00 - 1.02   0.99   0.98
+//  126 Mpx (120 x 1024^2)  0.98 - 1.00
+//  151 Mpx (36 x 2048^2)   1.00 - 1.03   0.99   0.98
+//  268 Mpx (64 x 2048^2)   1.01 - 1.05   1.00
+// so FP32 crosses at about 100 Mpx, within 2% either way from 84 to 126, and FP64 and
+// mixed batches gain at most 2% beyond it.
 constexpr double kFineBlockPx = 1e8;
 // The row-marching output pass from this many waves on: below it, the march of
 // 64 rows is longer (22 us) than the whole quad pass.
@@ -1149,10 +1156,6 @@ struct Run {
         return GDF_OK;
     }
 
-    // V-cycles until every slice meets tol (host checks the flags after each
-    // cycle).  With first = false, continues from the current iterates.  A
-    // captured schedule has no host checks: it holds `captured` cycles, which
-    // frozen slices skip on the device.
     // Slices still iterating after a graph that holds too few cycles for them:
     // marks their outputs to be formed again.
     gdf_status still_active(bool &any)
@@ -1164,6 +1167,10 @@ struct Run {
         return GDF_OK;
     }
 
+    // V-cycles until every slice meets tol (host checks the flags after each
+    // cycle).  With first = false, continues from the current iterates.  A
+    // captured schedule has no host checks: it holds `captured` cycles (0:
+    // max_cycles), which frozen slices skip on the device.
     gdf_status iterate(bool fp64, bool first = true, int captured = 0)
     {
         gdf_status r;
@@ -2143,8 +2150,8 @@ static gdf_status fuse_stack_plain(const uint8_t *stack_all, int S_all, int H, i
     if (st != GDF_ENOCONV || o.prec != GDF_PREC_FP32) return st;
     // Slices left above tol at the FP32 floor are re-solved by FP64 refinement
     // from their g_s (FP32) and the stack: from the returned g_s when there is
-    // one, else one slice at a time from g_s smoothed again into the front of
-    // the workspace (the re-solve uses the rest of it).
+    // one, else in groups, from g_s smoothed again into the front of the
+    // workspace (the re-solve uses the rest of it).
     std::vector<gdf_slice_desc> d(S);
     for (int z = 0; z < S; ++z) {
         d[z].H = H;

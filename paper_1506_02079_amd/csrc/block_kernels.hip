@@ -570,7 +570,9 @@ __global__ __launch_bounds__(kBlockWaves *kWave, sizeof(T) == 4 ? 4 : 2) void bl
 // and back up.  Each level is the pass above over its one tile; what one wave
 // writes and another reads goes through memory with a barrier between (the
 // workgroup's own CU, so no further fence).  A launch per pass costs 6.5 us on
-// levels this small, of which 3 are the launch and the item's table look-ups.
+// levels this small, of which 3 are the launch and the item's table look-ups; the
+// seven passes of 6 x 96 x 80 take 41 us in one, 5.8 each: dependent loads, LDS
+// reads and barriers.
 template <typename T>
 __global__ __launch_bounds__(kBlockWaves *kWave, sizeof(T) == 4 ? 4 : 2) void tail_kernel(TailLaunch t)
 {
@@ -690,14 +692,6 @@ hipError_t block_t(BlockKind k, bool periodic, bool level0, int sweeps, const Bl
 
 }  // namespace
 
-// Measured against what it replaced.  Neumann (the strip kernel's row march), per
-// pass of 3 sweeps: level 1 of 24 x 901 x 1100, 35 -> 18 us up and 27 -> 18 us
-// down; level 1 of 6 x 96 x 80 (one block a slice), 25 -> 6.7 and 21 -> 7.3 us.
-// Large levels gain least: all coarse passes of 64 x 2048^2, 1.61 -> 1.25 ms a
-// call; of 2 x 21504 x 26624, 6.80 -> 6.38 ms.  Periodic (one launch per
-// half-sweep over memory), 12 x 1024 x 1200: 8.0 -> 0.55 ms a call.  Regions of
-// 128 rows (16 per wave; less halo, 120 registers) were slower on every stack
-// but the largest, and there not faster.
 hipError_t launch_tail(bool fp64, const TailLaunch &t, hipStream_t s)
 {
     if (t.a.n_items <= 0) return hipSuccess;
@@ -713,6 +707,14 @@ hipError_t launch_block_fine(bool zero, int sweeps, bool sor, bool fp64, const B
     return zero ? fine_sw<float, true>(sweeps, sor, a, s) : fine_sw<float, false>(sweeps, sor, a, s);
 }
 
+// Measured against what it replaced.  Neumann (the strip kernel's row march), per
+// pass of 3 sweeps: level 1 of 24 x 901 x 1100, 35 -> 18 us up and 27 -> 18 us
+// down; level 1 of 6 x 96 x 80 (one block a slice), 25 -> 6.7 and 21 -> 7.3 us.
+// Large levels gain least: all coarse passes of 64 x 2048^2, 1.61 -> 1.25 ms a
+// call; of 2 x 21504 x 26624, 6.80 -> 6.38 ms.  Periodic (one launch per
+// half-sweep over memory), 12 x 1024 x 1200: 8.0 -> 0.55 ms a call.  Regions of
+// 128 rows (16 per wave; less halo, 120 registers) were slower on every stack
+// but the largest, and there not faster.
 hipError_t launch_block(BlockKind k, bool periodic, bool level0, int sweeps, bool fp64, const BlockLaunch &a,
                         hipStream_t s)
 {
