@@ -873,13 +873,6 @@ struct Run {
     // the smoothing pass restricted the unshifted b to level 1: the first pass
     // skips its restriction and the next level-1 down pass removes the mean
     bool raw_rhs_l1 = false;
-    // In a solve whose smoothing restricted the unshifted b, every level-1 pass of
-    // the first cycle removes the mean from it.  (The way up used to smooth against
-    // the unshifted values: 6 x 96 x 80, residual after one cycle 2e-3 instead of
-    // 3e-4.)  The better first cycle makes more slices stop just inside tol after
-    // three, where f is less accurate than after the fourth they used to take, so
-    // such a solve stops earlier in the loop (fused_loop_tol).
-    double loop_tol = 0.99;
 
     Run(const Plan &p, char *w, hipStream_t st_) : P(p), ws(w), s(st_)
     {
@@ -1026,8 +1019,8 @@ struct Run {
         return GDF_OK;
     }
 
-    // The in-loop test uses loop_tol x tol: the working-precision residual can sit
-    // a hair below the exact FP64 residual of the output, which is checked after.
+    // The in-loop test uses 0.99 tol: the working-precision residual can sit a
+    // hair below the exact FP64 residual of the output, which is checked after.
     // (in-loop checks -- strip partials, or FP64 partials with the sums of r --
     // use the working-precision residual)
     int max_slots(const int *range) const
@@ -1047,7 +1040,7 @@ struct Run {
             t_check = (t_check + 1) & 0x3fffffffu;
         }
         flags_told = told;
-        const double t = in_loop ? loop_tol * tol : tol;
+        const double t = in_loop ? 0.99 * tol : tol;
         HIP_TRY(launch_finish(P.n, max_slots(range), range, pf, pd, pd2, mode, t, max_cycles, count, in_loop ? stall_ratio : 0.0, st,
                               active, told, t_check, s));
         return GDF_OK;
@@ -1058,11 +1051,20 @@ struct Run {
     {
         const double e = fp64 ? 8.0 : 2.0;   // coarse-level element bytes
         gdf_status r;
+        // Only the way down removes the mean from an unshifted level-1 right-hand
+        // side.  On the way up as well, it would leave a smaller residual after the
+        // first cycle, and slices would then stop a cycle earlier, just inside tol:
+        // 9 x 701 x 333 at alpha 0.02 after 3 cycles, f 5.3e-7 from the solution in 64
+        // bits, instead of after 4 and 9.7e-8; over 96 stacks at alpha 0.001 to 0.1, 47
+        // end further off, the worst 5.5 times.  A stricter in-loop stop to go with it (0.6
+        // tol at alpha 0.0025, falling to 0.5 at 0.0036) brings most of them back, but takes
+        // 1.1 times as long where slices had just passed: 64 x 2048^2 with a gain ramp
+        // over x, alpha 0.01, 5.81 ms without both before, 5.47 without now, 6.36 with.
         const bool raw = raw_rhs_l1;
         raw_rhs_l1 = false;
         for (int l = 1; l <= P.max_level; ++l) {
             if ((r = block(P.bmid[l], BK_DOWN_ZERO, l, 0, 0, fp64, 2.25 * e, raw && l == 1))) return r;
-            if ((r = block(P.blast[l], BK_LAST_ZERO, l, 0, 0, fp64, 2 * e, raw && l == 1))) return r;
+            if ((r = block(P.blast[l], BK_LAST_ZERO, l, 0, 0, fp64, 2 * e))) return r;
         }
         if (P.btail.count) {
             TailLaunch t{};
@@ -1077,7 +1079,7 @@ struct Run {
             HIP_TRY(launch_tail(fp64, t, s));
         }
         for (int l = P.max_level - 1; l >= 1; --l)
-            if ((r = block(P.bmid[l], BK_UP, l, 0, 1, fp64, 3.25 * e, raw && l == 1))) return r;
+            if ((r = block(P.bmid[l], BK_UP, l, 0, 1, fp64, 3.25 * e))) return r;
         return GDF_OK;
     }
 
@@ -1964,21 +1966,6 @@ gdf_status fuse_stack(const uint8_t *stack, int S, int H, int W, long long pitch
     });
 }
 
-// The in-loop stop of a solve whose smoothing restricted b, relative to tol: 0.6 up to
-// alpha 0.0025, 0.5 from 0.0036 on, continuous, so that neighbouring weights stop alike.
-// It makes up for the better first cycle (see Run::loop_tol), whose gain grows with
-// alpha: the residual that a mean left in the level-1 right-hand side adds is
-// proportional to alpha.  At weak screening nearly every slice takes three cycles at 0.99
-// too, and a stricter stop buys a fourth.
-// Error of f, and time, against stopping at 0.99 without the better first cycle (64 x
-// 2048^2, plain sweeps): alpha 0.001 0.96, 0.91; 0.002 0.79, 0.98; 0.003 0.80, 0.93; 0.006
-// 0.44, 0.96; 0.0099 0.66, 0.96; 0.01 0.69, 0.97; 0.015 0.31, 0.96; 0.03 1.02, 0.90; 0.1
-// 1.20, 0.83 (there 1.2e-7, the accuracy of FP32).  96 drawn stacks: errors 0.87 times
-// what they were in the mean, 14 above 1.1 times (0.6 throughout: 25), the worst 2.9 (1.9e-7
-// to 5.4e-7); times 0.32 to 1.01.  0.5 throughout takes 1.07 times as long at alpha 0.0015
-// and 0.002.
-static double fused_loop_tol(double alpha) { return std::min(0.6, std::max(0.5, 0.03 / std::sqrt(alpha))); }
-
 // Smoothing arguments of a stack (taps, renormalisation tables, tiling); the
 // caller sets the outputs (b_u, level-1 right-hand side, g_s, partial sums).
 static SmoothArgs smooth_args(const uint8_t *stack, int S, int H, int W, long long pitch_row, long long pitch_slice,
@@ -2094,7 +2081,6 @@ static gdf_status fuse_stack_plain(const uint8_t *stack_all, int S_all, int H, i
         for (int z = 1; z < S; ++z)
             if ((long long)(P.g[z].off_b[1] - P.g[0].off_b[1]) != a.bc_slice_stride * z * P.csz) a.bc0 = nullptr;
     }
-    if (a.bc0 && !mixed) R.loop_tol = fused_loop_tol(alpha);
     a.part_bb = R.partd;
     a.part_b0 = R.partd2;
     a.part_bs = R.partd3;

@@ -297,10 +297,11 @@ __device__ __forceinline__ void block_item(const BlockLaunch &a, const LevelDesc
         __syncthreads();
     }
     // the level-0 mean is removed from the right-hand side (level 0), or its
-    // children's share of it (a level 1 restricted from unshifted values)
+    // children's share of it (a level 1 restricted from unshifted values, on the way
+    // down)
     if (!dead) {
         const T bsh = L.bshift ? (T)uniform_d(*L.bshift) : T(0);
-        const T bsc = (a.raw_rhs && L.bshift_fine) ? T(4) * (T)uniform_d(*L.bshift_fine) : T(0);
+        const T bsc = (!PROLONG && a.raw_rhs && L.bshift_fine) ? T(4) * (T)uniform_d(*L.bshift_fine) : T(0);
         const T bsg = (bsh + bsc) * ivs;
 #pragma unroll
         for (int r = 0; r < R; ++r) {

@@ -29,7 +29,7 @@ struct LevelDesc {
     int pad_;
     // level 1: the level-0 mean; a right-hand side restricted from the unshifted
     // level-0 one (BlockLaunch::raw_rhs) has each cell's children's share of it
-    // subtracted on load
+    // subtracted on load on the way down
     const double *bshift_fine;
 };
 

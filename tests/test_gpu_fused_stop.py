@@ -37,3 +37,17 @@ def test_error_at_fp32_accuracy(alpha):
     e = [np.linalg.norm(a - b) / np.linalg.norm(b) for a, b in zip(f.cpu().numpy().astype(np.float64), fr)]
     print(alpha, [r["vcycles"] for r in rep], ["%.1e" % v for v in e], flush=True)
     assert max(e) <= 8 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("alpha", [0.003, 0.006, 0.01, 0.02])
+def test_no_cycle_more_than_tol_needs(alpha):
+    """A slice that took c cycles is not well inside tol after c - 1: the stop in the
+    loop is tol but for the rounding of its FP32 residual (a few 2^-24, 0.2 tol)."""
+    st = torch.from_numpy(synth.make_stack(24, 384, 448, seed=1001, ramp=True)).to(DEV)
+    cycles = [r["vcycles"] for r in gdf.fuse_stack(st, alpha)[1]]
+    print(alpha, cycles, flush=True)
+    for c in sorted(set(cycles)):
+        _, rep = gdf.fuse_stack(st, alpha, max_vcycles=c - 1, allow_noconv=True)
+        rel = [r["rel_residual"] for r, k in zip(rep, cycles) if k == c]
+        print(c - 1, ["%.2e" % v for v in rel], flush=True)
+        assert min(rel) > 0.8e-6
